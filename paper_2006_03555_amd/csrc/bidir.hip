@@ -88,6 +88,10 @@ struct KsideSmem<T, M, 1> {
   KVTile<T> tl[1][2];
 };
 
+// A workgroup works on M of the Mall features a head's aggregate has: the
+// ngrp = Mall / M feature groups of a row split are separate workgroups (each
+// row of the aggregate is its own sum, so nothing is summed twice).
+//
 // AGG (backward pass): K holds the queries and V the output gradient; the value
 // rows are weighted by aux[t].x and aux[t].y takes the place of the ones column,
 // so the partials are sum_t Q-hat_t^T [a_t dout_t, e_t]. W'' is not stored.
@@ -97,8 +101,10 @@ __global__ __launch_bounds__(256 * NG, sizeof(T) == 2 && NG == 1 ? 2 : 1) void k
     const float *__restrict__ b, typename Mma<T>::frag *__restrict__ wfr,
     float *__restrict__ bqg, float *__restrict__ part, int H, int L, int rows_per_split,
     int nsplit, float s, float ws, float bs, float keps, int Mr, float cM,
-    const float2 *__restrict__ aux) {
-  const int item = xcd_item(blockIdx.x, gridDim.x);
+    const float2 *__restrict__ aux, int Mall, int ngrp) {
+  const int unit = xcd_item(blockIdx.x, gridDim.x);
+  const int item = unit / ngrp;
+  const int m0 = (unit - item * ngrp) * M;   // first feature of this workgroup
   const int bh = item / nsplit;
   const int split = item - bh * nsplit;
   constexpr int MW = M / 4;
@@ -128,15 +134,15 @@ __global__ __launch_bounds__(256 * NG, sizeof(T) == 2 && NG == 1 ? 2 : 1) void k
   TileRegs<T> rg;
   load_tile_regs<T>(rg, Kh, Vh, r0 + 64 * G, r1, tid);
 
-  fill_w_bfrags_lds<T, M, 256 * NG, KN>(sm.WB, sm.bq, W + (size_t)h * Mr * kD,
-                                        b + (size_t)h * Mr, ws, bs, Mr, keps);
+  fill_w_bfrags_lds<T, M, 256 * NG, KN>(sm.WB, sm.bq, W + ((size_t)h * Mr + m0) * kD,
+                                        b + (size_t)h * Mr + m0, ws, bs, Mr - m0, keps);
   __syncthreads();
-  // one workgroup per head stores W'' and b'' for later launches
+  // one workgroup per head and feature group stores W'' and b'' for later launches
   if (!AGG && bh < H && split == 0) {
     constexpr int NF = (M / 16) * 2 * 64;
-    frag *dst = wfr + (size_t)h * NF;
+    frag *dst = wfr + ((size_t)h * (Mall / 16) + m0 / 16) * 2 * 64;
     for (int i = threadIdx.x; i < NF; i += 256 * NG) dst[i] = (&sm.WB[0][0][0])[i];
-    if (threadIdx.x < M) bqg[(size_t)h * M + threadIdx.x] = sm.bq[threadIdx.x];
+    if (threadIdx.x < M) bqg[(size_t)h * Mall + m0 + threadIdx.x] = sm.bq[threadIdx.x];
   }
   frag Wf[MB][2];
   f32x4 bC[MB];
@@ -199,7 +205,7 @@ __global__ __launch_bounds__(256 * NG, sizeof(T) == 2 && NG == 1 ? 2 : 1) void k
     __syncthreads();
   }
 
-  float *dst = part + ((size_t)bh * nsplit + split) * M * 65;
+  float *dst = part + (((size_t)bh * nsplit + split) * Mall + m0) * 65;
   auto store_block = [&](int mb, const f32x4 (&a)[5]) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -429,6 +435,96 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void k_qside(const T *
   }
 }
 
+// The query side with the features split over the waves: wave w of the M / 32
+// projects its 32 features for the workgroup's 16 rows and contracts them
+// with its rows of Buf1, every operand straight from global memory into
+// registers; the waves' partial sums meet in LDS, added in wave order. A row
+// block then takes one feature step instead of M / 32 in turn, which is what a
+// call of few rows waits for.
+// k_qside's workgroups are bound by that chain (fp32 M 256: eight
+// steps of 72 products a row block) when they are too few to share CUs.
+// Measured against k_qside on the same calls (us): fp32 M 256, 1024 row blocks
+// 18.4 against 26.3, 2048 blocks 33.6 against 29.0; fp32 M 128, 1024 blocks 11.0
+// against 15.6; bf16 M 256, 256 / 512 / 1024 blocks 3.9 / 5.3 / 8.0 against
+// 8.9 / 8.8 / 9.2 (and slower at 2048: each row block reads W'' and Buf1 again).
+constexpr int kQsideSplitMaxBlocks = 1024;
+
+template <typename T, typename To, int M, int KN, int FIN, bool SAVE>
+__global__ __launch_bounds__(2 * M) void k_qside_split(
+    const T *__restrict__ Q, const typename Mma<T>::frag *__restrict__ wfr,
+    const float *__restrict__ bqg, const typename Mma<T>::frag *__restrict__ frags,
+    To *__restrict__ out, float *__restrict__ rsave, int H, int L, float s, float eps, float cM,
+    int ntiles) {
+  constexpr int NS = M / 32;   // waves
+  using P = Mma<T>;
+  using frag = typename P::frag;
+  __shared__ f32x4 num[NS][4][64];
+  __shared__ float den[NS][16];
+
+  const int w = threadIdx.x >> 6;
+  const int l = threadIdx.x & 63;
+  const int g = l >> 4;
+  const int c16 = l & 15;
+  const int item = xcd_item(blockIdx.x, gridDim.x);
+  const int bh = item / ntiles;
+  const int rbase = (item - bh * ntiles) * 16;
+  const int h = bh % H;
+
+  frag qf[1][2];
+  load_q_frags<T, 1>(qf, Q + (size_t)bh * L * kD, rbase, L);
+  f32x4 pf[2];
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {
+    const int mb = 2 * w + hh;
+    const frag *wp = wfr + ((size_t)h * (M / 16) + mb) * 2 * 64 + l;
+    const f32x4 bcv = *reinterpret_cast<const f32x4 *>(bqg + (size_t)h * M + mb * 16 + 4 * g);
+    f32x4 p = P::mma(wp[0], qf[0][0], bcv);
+    p = P::mma(wp[64], qf[0][1], p);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) pf[hh][j] = feature<KN, P>(p[j], bcv[j]);
+  }
+  const frag qb = P::pack(pf[0], pf[1]);
+  const frag *bp = frags + ((size_t)bh * 5 * NS + w) * 64 + l;
+#pragma unroll
+  for (int nb = 0; nb < 5; ++nb) {
+    const f32x4 o = P::mma(bp[(size_t)nb * NS * 64], qb, f32x4{0.f, 0.f, 0.f, 0.f});
+    if (nb < 4)
+      num[w][nb][l] = o;
+    else if (g == 0)
+      den[w][c16] = o[0];   // the denominator row is replicated
+  }
+  __syncthreads();
+
+  // waves 0 and 1: value columns 32 w + 8 g .. + 7 of row c16
+  if (w >= 2) return;
+  f32x4 a = num[0][2 * w][l], b = num[0][2 * w + 1][l];
+  float d = den[0][c16];
+#pragma unroll
+  for (int k = 1; k < NS; ++k) {
+    a += num[k][2 * w][l];
+    b += num[k][2 * w + 1][l];
+    d += den[k][c16];
+  }
+  // the stabiliser in units of the unscaled features, or the factor D_Q
+  // sqrt(2/M) the features omit, as in k_qside
+  float epsq = FIN == kFinDiv ? 0.f : FIN == kFinDivEps ? eps : 1.f;
+  if constexpr (KN == kCos && FIN != kFinDiv) {
+    float nrm = sq_sum16(qf[0]);
+    nrm += __shfl_xor(nrm, 16);
+    nrm += __shfl_xor(nrm, 32);
+    const float dq = cM * expf(0.5f * s * s * nrm);
+    epsq = FIN == kFinDivEps ? eps / dq : dq;
+  }
+  const int t = rbase + c16;
+  if (t < L) {
+    const float inv = FIN == kFinScale ? epsq : __builtin_amdgcn_rcpf(d + epsq);
+    if constexpr (SAVE) {
+      if (w == 0 && g == 0) rsave[(size_t)bh * L + t] = inv;
+    }
+    store8(out + ((size_t)bh * L + t) * kD + 32 * w + 8 * g, a * inv, b * inv);
+  }
+}
+
 // ---------------------------------------------------------------- launchers
 #define FAVOR_DISPATCH_M(M_, ...)                                   \
   switch (M_) {                                                     \
@@ -438,30 +534,37 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void k_qside(const T *
     default: return hipErrorInvalidValue;                           \
   }
 
+template <typename T, int M, int NG, int KN, bool AGG>
+static void kside_launch(const Shape &sh, const void *K, const void *V, const float *W,
+                         const float *b, void *wfr, float *bq, float *part, int rows_per_split,
+                         int nsplit, hipStream_t st, const float2 *aux) {
+  float ws, bs;
+  feature_scales(sh, ws, bs);
+  const int ngrp = sh.M / M;
+  hipLaunchKernelGGL((k_kside<T, M, NG, KN, AGG>), dim3(nsplit * sh.BH * ngrp), dim3(256 * NG), 0,
+                     st, (const T *)K, (const T *)V, W, b, (typename Mma<T>::frag *)wfr, bq, part,
+                     sh.H, sh.L, rows_per_split, nsplit, sh.s, ws, bs, sh.keps, sh.Mr,
+                     feature_norm(sh), aux, sh.M, ngrp);
+}
+
 template <int KN, bool AGG>
 static hipError_t kside_kernel(const Shape &sh, Dt in, const void *K, const void *V,
                                const float *W, const float *b, void *wfr, float *bq, float *part,
                                int rows_per_split, int nsplit, hipStream_t st,
                                const float2 *aux) {
-  dim3 grid(nsplit * sh.BH);
-  float ws, bs;
-  feature_scales(sh, ws, bs);
-  if (in == Dt::BF16) {
-    FAVOR_DISPATCH_M(sh.M,
-                     hipLaunchKernelGGL((k_kside<bf16, MM, kside_groups(Dt::BF16, MM), KN, AGG>),
-                                        grid, dim3(256 * kside_groups(Dt::BF16, MM)), 0, st,
-                                        (const bf16 *)K, (const bf16 *)V, W, b,
-                                        (Mma<bf16>::frag *)wfr, bq, part, sh.H, sh.L,
-                                        rows_per_split, nsplit, sh.s, ws, bs, sh.keps, sh.Mr,
-                                        feature_norm(sh), aux));
+#define FAVOR_KSIDE(T, MM, NG) \
+  kside_launch<T, MM, NG, KN, AGG>(sh, K, V, W, b, wfr, bq, part, rows_per_split, nsplit, st, aux)
+  if (nsplit * sh.BH < kKsideFeatureGroupBelow && sh.M > 64) {
+    if (in == Dt::BF16)
+      FAVOR_KSIDE(bf16, 64, 1);
+    else
+      FAVOR_KSIDE(float, 64, 1);
+  } else if (in == Dt::BF16) {
+    FAVOR_DISPATCH_M(sh.M, FAVOR_KSIDE(bf16, MM, kside_groups(Dt::BF16, MM)));
   } else {
-    FAVOR_DISPATCH_M(sh.M, hipLaunchKernelGGL((k_kside<float, MM, 1, KN, AGG>), grid, dim3(256),
-                                               0, st, (const float *)K, (const float *)V, W, b,
-                                               (Mma<float>::frag *)wfr, bq, part, sh.H, sh.L,
-                                               rows_per_split, nsplit, sh.s, ws, bs, sh.keps,
-                                               sh.Mr, feature_norm(sh),
-                                               aux));
+    FAVOR_DISPATCH_M(sh.M, FAVOR_KSIDE(float, MM, 1));
   }
+#undef FAVOR_KSIDE
   return hipGetLastError();
 }
 
@@ -504,6 +607,16 @@ template <typename T, typename To, int KN, int FIN, bool SAVE = false>
 static hipError_t qside_launch(const Shape &sh, const void *Q, const void *wfr, const float *bq,
                                const void *frags, void *o, hipStream_t st,
                                float *rsave = nullptr) {
+  const int blocks = (sh.L + 15) / 16;
+  if ((long long)sh.BH * blocks <= kQsideSplitMaxBlocks) {
+    FAVOR_DISPATCH_M(sh.M, hipLaunchKernelGGL((k_qside_split<T, To, MM, KN, FIN, SAVE>),
+                                              dim3(blocks * sh.BH), dim3(2 * MM), 0, st,
+                                              (const T *)Q, (const typename Mma<T>::frag *)wfr,
+                                              bq, (const typename Mma<T>::frag *)frags, (To *)o,
+                                              rsave, sh.H, sh.L, sh.s, sh.eps, feature_norm(sh),
+                                              blocks));
+    return hipGetLastError();
+  }
   const int rows = 64 * QsideCfg<T>::TBW;
   const int ntiles = (sh.L + rows - 1) / rows;
   const int nitems = ntiles * sh.BH;

@@ -61,6 +61,19 @@ constexpr int kMinRowsPerSplit = 256;
 // prologue (measured: the causal call 10-23% and its gradients 25-32% faster at
 // L <= 1024 for 32 heads; longer sequences keep the workgroup target's segments)
 constexpr int kMinRowsPerSegment = 128;
+// Rows per key-pass split at least, for the bidirectional call. A split of 256
+// rows amortises a workgroup's W'' build; while the chip is not full even with
+// one workgroup per 64 features of a split (favor::kKsideFeatureGroupBelow),
+// shorter splits take less time in spite of it. float32 B1 H1 L1024 M128, whole
+// call: 37.5 us with 256-row splits, 30.2 with 128, 27.1 with 64; B2 H8 L1024
+// M256 (full at 256 rows): 51.8, 57.0, 57.4.
+int min_split_rows(int BH, int tiles, int M) {
+  int rows = kMinRowsPerSplit;
+  while (rows > 64 && (long long)BH * ((tiles + rows / 64 - 1) / (rows / 64)) * (M / 64) <
+                          favor::kKsideFeatureGroupBelow)
+    rows /= 2;
+  return rows;
+}
 // Longest sequence per head (and longest causal segment): the kernels index
 // tokens with 32-bit integers and step past the end by up to two tiles.
 constexpr int kMaxL = 1 << 30;
@@ -206,7 +219,9 @@ Plan make_plan(const favor_desc *g, int op) {
                        : chunk_len(g) == kChunkSmall ? 2 * kCausalWorkgroups
                                                      : kCausalWorkgroups;
     int want = (target + p.BH - 1) / p.BH;
-    int max_split = tiles / ((causal ? kMinRowsPerSegment : kMinRowsPerSplit) / 64);
+    const int min_rows =
+        causal ? kMinRowsPerSegment : min_split_rows(p.BH, tiles, padded_m(g->M));
+    int max_split = tiles / (min_rows / 64);
     if (max_split < 1) max_split = 1;
     if (want > max_split) want = max_split;
     if (want < 1) want = 1;
