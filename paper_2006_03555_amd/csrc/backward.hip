@@ -555,12 +555,7 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dq_scan(
   const int s1 = s0 + SP::NS / 2;
   __syncthreads();
 
-  // the keys and values of a chunk (all four blocks in every wave). bf16: loaded
-  // one chunk ahead, once the previous chunk's are no longer read, and the row
-  // statistics are loaded at the top of the chunk but used after its barrier;
-  // fp32 fragments are twice as wide and take the chunk's loads at its top (the
-  // registers would not hold both)
-  constexpr bool kAhead = sizeof(T) == 2;
+  // the keys and values of a chunk (all four blocks in every wave)
   frag ka[4][2], va[4][2];
   auto load_kv = [&](int tc) __attribute__((always_inline)) {
 #pragma unroll
@@ -570,9 +565,8 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dq_scan(
       load_rows64<T>(va[tb], Vh, t, r1);
     }
   };
-  if (kAhead && r0 < r1) load_kv(r0);
   for (int t0 = r0; t0 < r1; t0 += 64) {
-    if constexpr (!kAhead) load_kv(t0);
+    load_kv(t0);
     // this row block's queries, output gradient, output and row scale
     const int i = t0 + 16 * qb + c16;
     frag qf[2], df[2], of[2];
@@ -580,33 +574,13 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dq_scan(
     load_rows64<T>(qf, Qh, i, r1);
     load_rows64<T>(df, dOh, i, r1);
     load_row_stats<T, RN>(of, rs, Oh, rsave + (size_t)bh * L, i, r1);
-    if constexpr (!kAhead)
-      row_weights_loaded<T, KN, RN>(qf, df, of, rs, i, r1, cM, s2half, alpha, ud);
+    row_weights_loaded<T, KN, RN>(qf, df, of, rs, i, r1, cM, s2half, alpha, ud);
     if (sw) chunk_features_t<T, FB, KN>(sm.KT, sm.WA, sm.bq, ka, w * FB);
     if (hf == 0) {   // C~ of key block qb
       const int t = t0 + 16 * qb + c16;
-      frag ko[2], vo[2];
-      if constexpr (kAhead) {
-        // the chunk's rows are held (loaded a chunk ahead); qb is uniform over
-        // the wave, so taking block qb is a scalar choice, not a runtime
-        // register index
-        const int qbu = __builtin_amdgcn_readfirstlane(qb);
-        ko[0] = ka[0][0];
-        ko[1] = ka[0][1];
-        vo[0] = va[0][0];
-        vo[1] = va[0][1];
-#pragma unroll
-        for (int tb = 1; tb < 4; ++tb)
-          if (tb == qbu) {
-            ko[0] = ka[tb][0];
-            ko[1] = ka[tb][1];
-            vo[0] = va[tb][0];
-            vo[1] = va[tb][1];
-          }
-      } else {   // fp32: loaded again (a runtime register index would go to scratch)
-        load_rows64<T>(ko, Kh, t, r1);
-        load_rows64<T>(vo, Vh, t, r1);
-      }
+      frag ko[2], vo[2];   // loaded again: a runtime register index would go to scratch
+      load_rows64<T>(ko, Kh, t, r1);
+      load_rows64<T>(vo, Vh, t, r1);
       float Do = 1.f;
       if constexpr (KN == kCos) Do = cM * expf(s2half * sq_norm16<T>(ko));
       Do = t < r1 ? Do : 0.f;
@@ -652,8 +626,6 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dq_scan(
         }
     }
 
-    if constexpr (kAhead)
-      row_weights_loaded<T, KN, RN>(qf, df, of, rs, i, r1, cM, s2half, alpha, ud);
     // queries of row block qb, feature steps [s0, s1)
     // P2[j][i] = D~_j (v_j . dout_i + u_d,i) for keys j <= i (B operand, k = keys)
     frag pb2[2];
@@ -671,8 +643,6 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dq_scan(
       pb2[0] = P::pack(pt[0], pt[1]);
       pb2[1] = P::pack(pt[2], pt[3]);
     }
-    // the chunk's keys and values are read for the last time above
-    if (kAhead && t0 + 64 < r1) load_kv(t0 + 64);
     f32x4 dacc[4];
     float dot2;
     query_grad<T, M, KN, true>(sm.WA, sm.bq, sm.WT, sm.SA, sm.sz, sm.KT, pb2, qf, df, alpha, ud,
@@ -971,39 +941,19 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dkv_scan(
   const float2 *auh = aux + (size_t)bh * L;
   __syncthreads();
 
-  // The dV pass with bf16 operands has registers to spare: the rows the next
-  // chunk in scan order reads (its keys, queries, output gradients and row
-  // weights) are loaded once this chunk has consumed its own, right after its
-  // first barrier, so that their latency hides behind this chunk's products;
-  // the key rows, read until the end of the chunk, go to a second buffer.
-  constexpr bool kAhead = !KPART && sizeof(T) == 2;
-  frag kf[2], vf[2], kfn[2], qa[4][2], dob[2], qo[2];
+  frag kf[2], vf[2], qa[4][2], dob[2], qo[2];
   float2 ao = make_float2(0.f, 0.f);
-  auto load_ahead = [&](int tc, frag (&kdst)[2]) __attribute__((always_inline)) {
-    const int t = tc + 16 * qb + c16;
-    load_rows64<T>(kdst, Kh, t, r1);
-#pragma unroll
-    for (int tb = 0; tb < 4; ++tb) load_rows64<T>(qa[tb], Qh, tc + 16 * tb + c16, r1);
-    if (hf == 0) {
-      load_rows64<T>(dob, dOh, t, r1);
-      ao = t < r1 ? auh[t] : make_float2(0.f, 0.f);
-    }
-    load_rows64<T>(qo, Qh, t, r1);
-  };
   const int nch = (r1 - r0 + 63) / 64;
-  if (kAhead && nch > 0) load_ahead(r0 + 64 * (nch - 1), kf);
   for (int c = nch - 1; c >= 0; --c) {
     const int t0 = r0 + 64 * c;
     // this row block's keys and values, loaded with the chunk's other rows
     const int j = t0 + 16 * qb + c16;
-    if constexpr (!kAhead) {
-      load_rows64<T>(kf, Kh, j, r1);
-      load_rows64<T>(vf, Vh, j, r1);
-      // the chunk's queries: features (row m) of the state waves' blocks, u~^T
-      // of row block qb; (alpha, alpha u_d) of every row
+    load_rows64<T>(kf, Kh, j, r1);
+    load_rows64<T>(vf, Vh, j, r1);
+    // the chunk's queries: features (row m) of the state waves' blocks, u~^T
+    // of row block qb; (alpha, alpha u_d) of every row
 #pragma unroll
-      for (int tb = 0; tb < 4; ++tb) load_rows64<T>(qa[tb], Qh, t0 + 16 * tb + c16, r1);
-    }
+    for (int tb = 0; tb < 4; ++tb) load_rows64<T>(qa[tb], Qh, t0 + 16 * tb + c16, r1);
     if (sw) chunk_features_t<T, FB, KN>(sm.QT, sm.WA, sm.bq, qa, w * FB);
     frag da[4][2];
     float2 au[4];
@@ -1028,7 +978,7 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dkv_scan(
             dob[1] = da[tb][1];
             ao = au[tb];
           }
-      } else if constexpr (!kAhead) {   // fp32 dV pass: loaded again
+      } else {   // dV pass: loaded again
         const int t = t0 + 16 * qb + c16;
         load_rows64<T>(dob, dOh, t, r1);
         ao = t < r1 ? auh[t] : make_float2(0.f, 0.f);
@@ -1058,7 +1008,7 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dkv_scan(
     }
     if constexpr (!KPART) {
       // row block qb's features with lane row = query (k = m), steps [s0, s1)
-      if constexpr (!kAhead) load_rows64<T>(qo, Qh, t0 + 16 * qb + c16, r1);
+      load_rows64<T>(qo, Qh, t0 + 16 * qb + c16, r1);
 #pragma unroll 2
       for (int sidx = s0; sidx < s1; ++sidx) {
         f32x4 f[2];
@@ -1093,10 +1043,6 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dkv_scan(
       }
     }
     __syncthreads();
-    if constexpr (kAhead) {
-      if (c > 0) load_ahead(t0 - 64, kfn);
-    }
-
     if (sw) {   // fold the chunk's rows into R
 #pragma unroll
       for (int mb = 0; mb < FB; ++mb)
@@ -1165,10 +1111,6 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dkv_scan(
           store_vgrad<T, ACC>(dV + ((size_t)bh * L + j) * kD, vacc, D);
       }
     }
-    if constexpr (kAhead) {
-      kf[0] = kfn[0];
-      kf[1] = kfn[1];
-    }
   }
 }
 
@@ -1200,6 +1142,7 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dkv_scan(
 template <typename T> constexpr int bwd_max_m(bool causal) {
   return sizeof(T) == 2 ? 256 : (causal ? 64 : 128);
 }
+
 
 // Scale of W in the input-gradient products: s for cos features (2 pi W'' = s W),
 // s / sqrt(M) for ReLU features (W'' itself).
@@ -1265,51 +1208,51 @@ static hipError_t with_acc(bool first, F &&f) {
   return f(std::false_type{});
 }
 
-// accumulate (causal only): every slice adds onto what dQ holds (the other
-// direction's gradient, when both are differentiated in one call).
-template <typename T>
-static hipError_t bwd_dq_typed(const Shape &sh, bool causal, const BwdArgs &a, hipStream_t st,
-                               bool accumulate) {
+// Causal scans of fp32 inputs (bf16: backward_scan.hip). accumulate: every slice
+// adds onto what dQ holds (the other direction's gradient, when both are
+// differentiated in one call).
+static hipError_t causal_dq_f32(const Shape &sh, const BwdArgs &a, hipStream_t st,
+                                bool accumulate) {
+  using T = float;
   const float wts = wt_scale(sh);
   return bwd_variant(sh, [&](auto kn, auto rn) -> hipError_t {
     constexpr int KN = decltype(kn)::value;
     constexpr bool RN = decltype(rn)::value;
-    return over_slices<T>(sh, causal, [&](int ms, int m0, bool first) -> hipError_t {
-      if (causal && accumulate) {
-        dim3 grid(a.nseg * sh.BH);
-        FAVOR_BWD_DISPATCH_M(bwd_max_m<T>(true), ms,
-            hipLaunchKernelGGL((k_bwd_dq_scan<T, MM, KN, RN, true>), grid, dim3(kScanThreads),
-                               0, st, (const T *)a.Q, (const T *)a.K, (const T *)a.V,
-                               (const T *)a.dout, (const T *)a.out, a.rsave,
-                               (const typename Mma<T>::frag *)a.wfr, a.bq, a.W, a.state,
-                               (T *)a.dQ, a.aux, sh.H, sh.L, a.seg_len, a.nseg, sh.s, sh.Mr,
-                               feature_norm(sh), sh.M, m0, wts));
+    return over_slices<T>(sh, true, [&](int, int m0, bool first) -> hipError_t {
+      return with_acc<T>(first && !accumulate, [&](auto acc) -> hipError_t {
+        constexpr bool ACC = decltype(acc)::value;
+        hipLaunchKernelGGL((k_bwd_dq_scan<T, bwd_max_m<T>(true), KN, RN, ACC>),
+                           dim3(a.nseg * sh.BH), dim3(kScanThreads), 0, st, (const T *)a.Q,
+                           (const T *)a.K, (const T *)a.V, (const T *)a.dout, (const T *)a.out,
+                           a.rsave, (const Mma<T>::frag *)a.wfr, a.bq, a.W, a.state, (T *)a.dQ,
+                           a.aux, sh.H, sh.L, a.seg_len, a.nseg, sh.s, sh.Mr, feature_norm(sh),
+                           sh.M, m0, wts);
         return hipGetLastError();
-      }
+      });
+    });
+  });
+}
+
+template <typename T>
+static hipError_t bidir_dq(const Shape &sh, const BwdArgs &a, hipStream_t st) {
+  const float wts = wt_scale(sh);
+  return bwd_variant(sh, [&](auto kn, auto rn) -> hipError_t {
+    constexpr int KN = decltype(kn)::value;
+    constexpr bool RN = decltype(rn)::value;
+    return over_slices<T>(sh, false, [&](int ms, int m0, bool first) -> hipError_t {
       return with_acc<T>(first, [&](auto acc) -> hipError_t {
         constexpr bool ACC = decltype(acc)::value;
-        if (causal) {
-          dim3 grid(a.nseg * sh.BH);
-          FAVOR_BWD_DISPATCH_M(bwd_max_m<T>(true), ms,
-              hipLaunchKernelGGL((k_bwd_dq_scan<T, MM, KN, RN, ACC>), grid, dim3(kScanThreads),
-                                 0, st, (const T *)a.Q, (const T *)a.K, (const T *)a.V,
-                                 (const T *)a.dout, (const T *)a.out, a.rsave,
-                                 (const typename Mma<T>::frag *)a.wfr, a.bq, a.W, a.state,
-                                 (T *)a.dQ, a.aux, sh.H, sh.L, a.seg_len, a.nseg, sh.s, sh.Mr,
-                                 feature_norm(sh), sh.M, m0, wts));
-        } else {
-          const int rows = kBwdBidirThreads / 4 * kBwdTbw;
-          const int ntiles = (sh.L + rows - 1) / rows;
-          const int nitems = ntiles * sh.BH;
-          dim3 grid(min(nitems, kBwdMaxWorkgroups));
-          FAVOR_BWD_DISPATCH_M(bwd_max_m<T>(false), ms,
-              hipLaunchKernelGGL((k_bwd_dq<T, MM, KN, RN, kBwdTbw, ACC>), grid,
-                                 dim3(kBwdBidirThreads), 0, st, (const T *)a.Q,
-                                 (const T *)a.dout, (const T *)a.out, a.rsave,
-                                 (const typename Mma<T>::frag *)a.wfr, a.bq, a.W, a.state,
-                                 (T *)a.dQ, a.aux, sh.H, sh.L, sh.s, sh.Mr, feature_norm(sh),
-                                 sh.M, m0, wts, ntiles, nitems));
-        }
+        const int rows = kBwdBidirThreads / 4 * kBwdTbw;
+        const int ntiles = (sh.L + rows - 1) / rows;
+        const int nitems = ntiles * sh.BH;
+        dim3 grid(min(nitems, kBwdMaxWorkgroups));
+        FAVOR_BWD_DISPATCH_M(bwd_max_m<T>(false), ms,
+            hipLaunchKernelGGL((k_bwd_dq<T, MM, KN, RN, kBwdTbw, ACC>), grid,
+                               dim3(kBwdBidirThreads), 0, st, (const T *)a.Q,
+                               (const T *)a.dout, (const T *)a.out, a.rsave,
+                               (const typename Mma<T>::frag *)a.wfr, a.bq, a.W, a.state,
+                               (T *)a.dQ, a.aux, sh.H, sh.L, sh.s, sh.Mr, feature_norm(sh),
+                               sh.M, m0, wts, ntiles, nitems));
         return hipGetLastError();
       });
     });
@@ -1318,46 +1261,54 @@ static hipError_t bwd_dq_typed(const Shape &sh, bool causal, const BwdArgs &a, h
 
 hipError_t launch_bwd_dq(const Shape &sh, Dt in, bool causal, const BwdArgs &a, hipStream_t st,
                          bool accumulate) {
-  if (in == Dt::BF16) return bwd_dq_typed<bf16>(sh, causal, a, st, accumulate);
-  return bwd_dq_typed<float>(sh, causal, a, st, accumulate);
+  if (causal)
+    return in == Dt::BF16 ? launch_bwd_dq_scan(sh, a, accumulate, st)
+                          : causal_dq_f32(sh, a, st, accumulate);
+  return in == Dt::BF16 ? bidir_dq<bf16>(sh, a, st) : bidir_dq<float>(sh, a, st);
 }
 
-template <typename T>
-static hipError_t bwd_dkv_typed(const Shape &sh, bool causal, const BwdArgs &a, hipStream_t st) {
+static hipError_t causal_dkv_f32(const Shape &sh, const BwdArgs &a, hipStream_t st) {
+  using T = float;
   const float wts = wt_scale(sh);
   return bwd_variant(sh, [&](auto kn, auto) -> hipError_t {
     constexpr int KN = decltype(kn)::value;
-    return over_slices<T>(sh, causal, [&](int ms, int m0, bool first) -> hipError_t {
+    return over_slices<T>(sh, true, [&](int, int m0, bool first) -> hipError_t {
       return with_acc<T>(first, [&](auto acc) -> hipError_t {
         constexpr bool ACC = decltype(acc)::value;
-        if (causal) {
-          dim3 grid(a.nseg * sh.BH);
-          FAVOR_BWD_DISPATCH_M(bwd_max_m<T>(true), ms, {
-            hipLaunchKernelGGL((k_bwd_dkv_scan<T, MM, KN, false, ACC>), grid,
-                               dim3(kScanThreads), 0, st, (const T *)a.Q, (const T *)a.K,
-                               (const T *)a.V, (const T *)a.dout, a.aux,
+        const auto launch = [&](auto key) {
+          hipLaunchKernelGGL(
+              (k_bwd_dkv_scan<T, bwd_max_m<T>(true), KN, decltype(key)::value, ACC>),
+              dim3(a.nseg * sh.BH), dim3(kScanThreads), 0, st, (const T *)a.Q, (const T *)a.K,
+              (const T *)a.V, (const T *)a.dout, a.aux, (const Mma<T>::frag *)a.wfr, a.bq, a.W,
+              a.state, (T *)a.dK, (T *)a.dV, sh.H, sh.L, a.seg_len, a.nseg, sh.s, sh.Mr,
+              feature_norm(sh), sh.M, m0, wts);
+        };
+        launch(std::false_type{});
+        launch(std::true_type{});
+        return hipGetLastError();
+      });
+    });
+  });
+}
+
+template <typename T>
+static hipError_t bidir_dkv(const Shape &sh, const BwdArgs &a, hipStream_t st) {
+  const float wts = wt_scale(sh);
+  return bwd_variant(sh, [&](auto kn, auto) -> hipError_t {
+    constexpr int KN = decltype(kn)::value;
+    return over_slices<T>(sh, false, [&](int ms, int m0, bool first) -> hipError_t {
+      return with_acc<T>(first, [&](auto acc) -> hipError_t {
+        constexpr bool ACC = decltype(acc)::value;
+        const int rows = kBwdBidirThreads / 4 * kBwdTbw;
+        const int ntiles = (sh.L + rows - 1) / rows;
+        const int nitems = ntiles * sh.BH;
+        dim3 grid(min(nitems, kBwdMaxWorkgroups));
+        FAVOR_BWD_DISPATCH_M(bwd_max_m<T>(false), ms,
+            hipLaunchKernelGGL((k_bwd_dkv<T, MM, KN, kBwdTbw, ACC>), grid,
+                               dim3(kBwdBidirThreads), 0, st, (const T *)a.K, (const T *)a.V,
                                (const typename Mma<T>::frag *)a.wfr, a.bq, a.W, a.state,
-                               (T *)a.dK, (T *)a.dV, sh.H, sh.L, a.seg_len, a.nseg, sh.s, sh.Mr,
-                               feature_norm(sh), sh.M, m0, wts);
-            hipLaunchKernelGGL((k_bwd_dkv_scan<T, MM, KN, true, ACC>), grid,
-                               dim3(kScanThreads), 0, st, (const T *)a.Q, (const T *)a.K,
-                               (const T *)a.V, (const T *)a.dout, a.aux,
-                               (const typename Mma<T>::frag *)a.wfr, a.bq, a.W, a.state,
-                               (T *)a.dK, (T *)a.dV, sh.H, sh.L, a.seg_len, a.nseg, sh.s, sh.Mr,
-                               feature_norm(sh), sh.M, m0, wts);
-          });
-        } else {
-          const int rows = kBwdBidirThreads / 4 * kBwdTbw;
-          const int ntiles = (sh.L + rows - 1) / rows;
-          const int nitems = ntiles * sh.BH;
-          dim3 grid(min(nitems, kBwdMaxWorkgroups));
-          FAVOR_BWD_DISPATCH_M(bwd_max_m<T>(false), ms,
-              hipLaunchKernelGGL((k_bwd_dkv<T, MM, KN, kBwdTbw, ACC>), grid,
-                                 dim3(kBwdBidirThreads), 0, st, (const T *)a.K, (const T *)a.V,
-                                 (const typename Mma<T>::frag *)a.wfr, a.bq, a.W, a.state,
-                                 (T *)a.dK, (T *)a.dV, sh.H, sh.L, sh.s, sh.Mr,
-                                 feature_norm(sh), sh.M, m0, wts, ntiles, nitems));
-        }
+                               (T *)a.dK, (T *)a.dV, sh.H, sh.L, sh.s, sh.Mr,
+                               feature_norm(sh), sh.M, m0, wts, ntiles, nitems));
         return hipGetLastError();
       });
     });
@@ -1365,8 +1316,9 @@ static hipError_t bwd_dkv_typed(const Shape &sh, bool causal, const BwdArgs &a, 
 }
 
 hipError_t launch_bwd_dkv(const Shape &sh, Dt in, bool causal, const BwdArgs &a, hipStream_t st) {
-  if (in == Dt::BF16) return bwd_dkv_typed<bf16>(sh, causal, a, st);
-  return bwd_dkv_typed<float>(sh, causal, a, st);
+  if (causal)
+    return in == Dt::BF16 ? launch_bwd_dkv_scan(sh, a, st) : causal_dkv_f32(sh, a, st);
+  return in == Dt::BF16 ? bidir_dkv<bf16>(sh, a, st) : bidir_dkv<float>(sh, a, st);
 }
 
 }  // namespace favor

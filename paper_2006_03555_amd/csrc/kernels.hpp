@@ -117,11 +117,15 @@ struct BwdArgs {
   void *dQ, *dK, *dV;
   float2 *aux;           // [BH][L] (alpha, alpha u_d)
   int seg_len, nseg;     // causal: the segments of the forward plan
+  float *kdot;           // causal bf16: [BH][L] scratch from dV to dK (h . k-hat per key)
 };
 // accumulate (causal only): add onto dQ instead of overwriting it.
 hipError_t launch_bwd_dq(const Shape &sh, Dt in, bool causal, const BwdArgs &a, hipStream_t st,
                          bool accumulate = false);
 hipError_t launch_bwd_dkv(const Shape &sh, Dt in, bool causal, const BwdArgs &a, hipStream_t st);
+// The causal gradients of bf16 inputs (backward_scan.hip).
+hipError_t launch_bwd_dq_scan(const Shape &sh, const BwdArgs &a, bool accumulate, hipStream_t st);
+hipError_t launch_bwd_dkv_scan(const Shape &sh, const BwdArgs &a, hipStream_t st);
 // Fixed-order sum of split partials [BH][ns][M][65] -> [BH][M][65].
 hipError_t launch_sum_splits(const Shape &sh, const float *part, int ns, float *dst,
                              hipStream_t st);
