@@ -395,7 +395,7 @@ __device__ __forceinline__ void row_weights(const typename Mma<T>::frag (&qf)[2]
   row_weights_loaded<T, KN, RN>(qf, df, of, rs, i, L, cM, s2half, alpha, ud);
 }
 
-// ------------------------------------------------------------ bidirectional dQ
+// ------------------------------------------------------------ bidirectional dQ (bf16)
 template <typename T, int M>
 struct DqSmem {
   using frag = typename Mma<T>::frag;
@@ -408,13 +408,13 @@ struct DqSmem {
 
 // Items are (head, tile of 8 waves x TBW x 16 rows), walked persistently over
 // XCD-local ranges; Buf1 [BH][M][65] fp32.
-template <typename T, int M, int KN, bool RN, int TBW, bool ACC>
+template <typename T, int M, int KN, bool RN, int TBW>
 __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dq(
     const T *__restrict__ Q, const T *__restrict__ dout, const T *__restrict__ out,
     const float *__restrict__ rsave, const typename Mma<T>::frag *__restrict__ wfr,
     const float *__restrict__ bqg, const float *__restrict__ W, const float *__restrict__ buf1,
     T *__restrict__ dQ, float2 *__restrict__ aux, int H, int L, float s, int Mr, float cM,
-    int Mall, int m0, float wts, int ntiles, int nitems) {
+    float wts, int ntiles, int nitems) {
   using frag = typename Mma<T>::frag;
   __shared__ DqSmem<T, M> sm;
   const int tid = threadIdx.x;
@@ -431,10 +431,10 @@ __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dq(
     const int h = bh % H;
     if (bh != cur) {
       __syncthreads();
-      copy_frags_wg<frag, (M / 16) * 2 * 64>(&sm.WA[0][0][0], wfr + ((size_t)h * (Mall / 16) + m0 / 16) * 2 * 64);
-      if (tid < M) sm.bq[tid] = bqg[(size_t)h * Mall + m0 + tid];
-      build_wt<T, M>(sm.WT, W + ((size_t)h * Mr + m0) * kD, wts, Mr - m0);
-      build_state_rows<T, M>(sm.SA, sm.sz, buf1 + ((size_t)bh * Mall + m0) * 65);
+      copy_frags_wg<frag, (M / 16) * 2 * 64>(&sm.WA[0][0][0], wfr + (size_t)h * (M / 16) * 2 * 64);
+      if (tid < M) sm.bq[tid] = bqg[(size_t)h * M + tid];
+      build_wt<T, M>(sm.WT, W + (size_t)h * Mr * kD, wts, Mr);
+      build_state_rows<T, M>(sm.SA, sm.sz, buf1 + (size_t)bh * M * 65);
       cur = bh;
       __syncthreads();
     }
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dq(
       query_grad<T, M, KN, false>(sm.WA, sm.bq, sm.WT, sm.SA, sm.sz, nullptr, none, qf, df, alpha,
                                   ud, s, dacc, dot2);
       if (i < L) {
-        store_qgrad<T, KN, ACC>(dQ + ((size_t)bh * L + i) * kD, dacc, qf, alpha, dot2, s);
+        store_qgrad<T, KN>(dQ + ((size_t)bh * L + i) * kD, dacc, qf, alpha, dot2, s);
         if (g == 0) aux[(size_t)bh * L + i] = make_float2(alpha, alpha * ud);
       }
     }
@@ -783,7 +783,7 @@ __device__ __forceinline__ void store_vgrad(T *dst, const f32x4 (&vacc)[4], floa
     put8<ACC>(dst + 32 * pp + 8 * g, vacc[2 * pp] * D, vacc[2 * pp + 1] * D);
 }
 
-// ------------------------------------------------------------ bidirectional dK, dV
+// ------------------------------------------------------------ bidirectional dK, dV (bf16)
 template <typename T, int M>
 struct DkvSmem {
   using frag = typename Mma<T>::frag;
@@ -795,13 +795,12 @@ struct DkvSmem {
   frag RB[4][M / 32][64];   // dBuf1 value columns over features
 };
 
-template <typename T, int M, int KN, int TBW, bool ACC>
+template <typename T, int M, int KN, int TBW>
 __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dkv(
     const T *__restrict__ K, const T *__restrict__ V,
     const typename Mma<T>::frag *__restrict__ wfr, const float *__restrict__ bqg,
     const float *__restrict__ W, const float *__restrict__ dbuf1, T *__restrict__ dK,
-    T *__restrict__ dV, int H, int L, float s, int Mr, float cM, int Mall, int m0, float wts,
-    int ntiles, int nitems) {
+    T *__restrict__ dV, int H, int L, float s, int Mr, float cM, float wts, int ntiles, int nitems) {
   using frag = typename Mma<T>::frag;
   __shared__ DkvSmem<T, M> sm;
   const int tid = threadIdx.x;
@@ -817,10 +816,10 @@ __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dkv(
     const int h = bh % H;
     if (bh != cur) {
       __syncthreads();
-      copy_frags_wg<frag, (M / 16) * 2 * 64>(&sm.WA[0][0][0], wfr + ((size_t)h * (Mall / 16) + m0 / 16) * 2 * 64);
-      if (tid < M) sm.bq[tid] = bqg[(size_t)h * Mall + m0 + tid];
-      build_wt<T, M>(sm.WT, W + ((size_t)h * Mr + m0) * kD, wts, Mr - m0);
-      const float *Rs = dbuf1 + ((size_t)bh * Mall + m0) * 65;
+      copy_frags_wg<frag, (M / 16) * 2 * 64>(&sm.WA[0][0][0], wfr + (size_t)h * (M / 16) * 2 * 64);
+      if (tid < M) sm.bq[tid] = bqg[(size_t)h * M + tid];
+      build_wt<T, M>(sm.WT, W + (size_t)h * Mr * kD, wts, Mr);
+      const float *Rs = dbuf1 + (size_t)bh * M * 65;
       build_state_rows<T, M>(sm.RA, sm.rz, Rs);
       build_state_cols<T, M>(sm.RB, Rs);
       cur = bh;
@@ -843,8 +842,8 @@ __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dkv(
                                             none, nullptr, nullptr, kf, vf, 0, kacc, doth,
                                             vacc);
       if (j < L) {
-        store_kgrad<T, KN, ACC>(dK + ((size_t)bh * L + j) * kD, kacc, kf, D, doth, s);
-        store_vgrad<T, ACC>(dV + ((size_t)bh * L + j) * kD, vacc, D);
+        store_kgrad<T, KN>(dK + ((size_t)bh * L + j) * kD, kacc, kf, D, doth, s);
+        store_vgrad<T>(dV + ((size_t)bh * L + j) * kD, vacc, D);
       }
     }
   }
@@ -1115,34 +1114,17 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dkv_scan(
 }
 
 // ------------------------------------------------------------ launchers
-// M dispatch up to MAX_ (fp32 operands double the LDS tables: the fp32
-// kernels stop at M = 128 bidirectional and M = 64 causal).
-#define FAVOR_BWD_DISPATCH_M(MAX_, M_, ...)                                \
-  switch (M_) {                                                            \
-    case 64: { constexpr int MM = 64; __VA_ARGS__; } break;                 \
-    case 128:                                                              \
-      if constexpr (MAX_ >= 128) {                                          \
-        constexpr int MM = 128;                                            \
-        __VA_ARGS__;                                                       \
-        break;                                                             \
-      } else {                                                             \
-        return hipErrorInvalidValue;                                       \
-      }                                                                    \
-    case 256:                                                              \
-      if constexpr (MAX_ >= 256) {                                          \
-        constexpr int MM = 256;                                            \
-        __VA_ARGS__;                                                       \
-        break;                                                             \
-      } else {                                                             \
-        return hipErrorInvalidValue;                                       \
-      }                                                                    \
-    default: return hipErrorInvalidValue;                                  \
+#define FAVOR_BWD_DISPATCH_M(M_, ...)                                \
+  switch (M_) {                                                     \
+    case 64: { constexpr int MM = 64; __VA_ARGS__; } break;          \
+    case 128: { constexpr int MM = 128; __VA_ARGS__; } break;        \
+    case 256: { constexpr int MM = 256; __VA_ARGS__; } break;        \
+    default: return hipErrorInvalidValue;                           \
   }
 
-template <typename T> constexpr int bwd_max_m(bool causal) {
-  return sizeof(T) == 2 ? 256 : (causal ? 64 : 128);
-}
-
+// Features the fp32 causal scans take at a time (fp32 operands double the LDS
+// tables).
+constexpr int kF32ScanM = 64;
 
 // Scale of W in the input-gradient products: s for cos features (2 pi W'' = s W),
 // s / sqrt(M) for ReLU features (W'' itself).
@@ -1183,29 +1165,20 @@ static hipError_t bwd_variant(const Shape &sh, F &&f) {
   return sh.renorm ? f(cosk{}, std::true_type{}) : f(cosk{}, std::false_type{});
 }
 
-// Feature slices of the gradient launches. A gradient is a sum over features
+// Feature slices of the fp32 causal launches. A gradient is a sum over features
 // once the per-row weights (out, r, alpha) are fixed, so a shape wider than the
-// kernels' LDS tables (fp32 operands: bwd_max_m features) runs as slices
-// [m0, m0 + ms) of the M rows, the slices after the first adding into the fp32
-// gradients; slices wholly past the M_r features drawn add nothing and are
-// skipped. f(ms, m0, first) launches one slice.
-template <typename T, typename F>
-static hipError_t over_slices(const Shape &sh, bool causal, F &&f) {
-  const int ms = sh.M < bwd_max_m<T>(causal) ? sh.M : bwd_max_m<T>(causal);
-  for (int m0 = 0; m0 < sh.M && m0 < sh.Mr; m0 += ms) {
-    const hipError_t e = f(ms, m0, m0 == 0);
+// kernels' LDS tables runs as slices [m0, m0 + kF32ScanM) of the M rows, the slices
+// after the first (or, with accumulate, every one) adding into the gradients;
+// slices wholly past the M_r features drawn add nothing and are skipped.
+// f(m0, bool_constant add) launches one slice.
+template <typename F>
+static hipError_t over_slices(const Shape &sh, bool accumulate, F &&f) {
+  for (int m0 = 0; m0 < sh.M && m0 < sh.Mr; m0 += kF32ScanM) {
+    const hipError_t e =
+        m0 > 0 || accumulate ? f(m0, std::true_type{}) : f(m0, std::false_type{});
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
-}
-
-// Calls f(bool_constant ACC): false for the first slice, true after it (fp32 only).
-template <typename T, typename F>
-static hipError_t with_acc(bool first, F &&f) {
-  if constexpr (sizeof(T) == 4) {
-    if (!first) return f(std::true_type{});
-  }
-  return f(std::false_type{});
 }
 
 // Causal scans of fp32 inputs (bf16: backward_scan.hip). accumulate: every slice
@@ -1218,44 +1191,34 @@ static hipError_t causal_dq_f32(const Shape &sh, const BwdArgs &a, hipStream_t s
   return bwd_variant(sh, [&](auto kn, auto rn) -> hipError_t {
     constexpr int KN = decltype(kn)::value;
     constexpr bool RN = decltype(rn)::value;
-    return over_slices<T>(sh, true, [&](int, int m0, bool first) -> hipError_t {
-      return with_acc<T>(first && !accumulate, [&](auto acc) -> hipError_t {
-        constexpr bool ACC = decltype(acc)::value;
-        hipLaunchKernelGGL((k_bwd_dq_scan<T, bwd_max_m<T>(true), KN, RN, ACC>),
-                           dim3(a.nseg * sh.BH), dim3(kScanThreads), 0, st, (const T *)a.Q,
-                           (const T *)a.K, (const T *)a.V, (const T *)a.dout, (const T *)a.out,
-                           a.rsave, (const Mma<T>::frag *)a.wfr, a.bq, a.W, a.state, (T *)a.dQ,
-                           a.aux, sh.H, sh.L, a.seg_len, a.nseg, sh.s, sh.Mr, feature_norm(sh),
-                           sh.M, m0, wts);
-        return hipGetLastError();
-      });
+    return over_slices(sh, accumulate, [&](int m0, auto acc) -> hipError_t {
+      constexpr bool ACC = decltype(acc)::value;
+      hipLaunchKernelGGL((k_bwd_dq_scan<T, kF32ScanM, KN, RN, ACC>), dim3(a.nseg * sh.BH),
+                         dim3(kScanThreads), 0, st, (const T *)a.Q, (const T *)a.K,
+                         (const T *)a.V, (const T *)a.dout, (const T *)a.out, a.rsave,
+                         (const Mma<T>::frag *)a.wfr, a.bq, a.W, a.state, (T *)a.dQ, a.aux, sh.H,
+                         sh.L, a.seg_len, a.nseg, sh.s, sh.Mr, feature_norm(sh), sh.M, m0, wts);
+      return hipGetLastError();
     });
   });
 }
 
-template <typename T>
-static hipError_t bidir_dq(const Shape &sh, const BwdArgs &a, hipStream_t st) {
-  const float wts = wt_scale(sh);
+static hipError_t bidir_dq_bf16(const Shape &sh, const BwdArgs &a, hipStream_t st) {
+  using T = bf16;
+  const int rows = kBwdBidirThreads / 4 * kBwdTbw;
+  const int ntiles = (sh.L + rows - 1) / rows;
+  const int nitems = ntiles * sh.BH;
+  dim3 grid(min(nitems, kBwdMaxWorkgroups));
   return bwd_variant(sh, [&](auto kn, auto rn) -> hipError_t {
     constexpr int KN = decltype(kn)::value;
     constexpr bool RN = decltype(rn)::value;
-    return over_slices<T>(sh, false, [&](int ms, int m0, bool first) -> hipError_t {
-      return with_acc<T>(first, [&](auto acc) -> hipError_t {
-        constexpr bool ACC = decltype(acc)::value;
-        const int rows = kBwdBidirThreads / 4 * kBwdTbw;
-        const int ntiles = (sh.L + rows - 1) / rows;
-        const int nitems = ntiles * sh.BH;
-        dim3 grid(min(nitems, kBwdMaxWorkgroups));
-        FAVOR_BWD_DISPATCH_M(bwd_max_m<T>(false), ms,
-            hipLaunchKernelGGL((k_bwd_dq<T, MM, KN, RN, kBwdTbw, ACC>), grid,
-                               dim3(kBwdBidirThreads), 0, st, (const T *)a.Q,
-                               (const T *)a.dout, (const T *)a.out, a.rsave,
-                               (const typename Mma<T>::frag *)a.wfr, a.bq, a.W, a.state,
-                               (T *)a.dQ, a.aux, sh.H, sh.L, sh.s, sh.Mr, feature_norm(sh),
-                               sh.M, m0, wts, ntiles, nitems));
-        return hipGetLastError();
-      });
-    });
+    FAVOR_BWD_DISPATCH_M(sh.M,
+        hipLaunchKernelGGL((k_bwd_dq<T, MM, KN, RN, kBwdTbw>), grid, dim3(kBwdBidirThreads), 0,
+                           st, (const T *)a.Q, (const T *)a.dout, (const T *)a.out, a.rsave,
+                           (const Mma<T>::frag *)a.wfr, a.bq, a.W, a.state, (T *)a.dQ, a.aux,
+                           sh.H, sh.L, sh.s, sh.Mr, feature_norm(sh), wt_scale(sh), ntiles,
+                           nitems));
+    return hipGetLastError();
   });
 }
 
@@ -1264,7 +1227,7 @@ hipError_t launch_bwd_dq(const Shape &sh, Dt in, bool causal, const BwdArgs &a, 
   if (causal)
     return in == Dt::BF16 ? launch_bwd_dq_scan(sh, a, accumulate, st)
                           : causal_dq_f32(sh, a, st, accumulate);
-  return in == Dt::BF16 ? bidir_dq<bf16>(sh, a, st) : bidir_dq<float>(sh, a, st);
+  return in == Dt::BF16 ? bidir_dq_bf16(sh, a, st) : launch_bwd_dq_f32(sh, a, st);
 }
 
 static hipError_t causal_dkv_f32(const Shape &sh, const BwdArgs &a, hipStream_t st) {
@@ -1272,53 +1235,44 @@ static hipError_t causal_dkv_f32(const Shape &sh, const BwdArgs &a, hipStream_t 
   const float wts = wt_scale(sh);
   return bwd_variant(sh, [&](auto kn, auto) -> hipError_t {
     constexpr int KN = decltype(kn)::value;
-    return over_slices<T>(sh, true, [&](int, int m0, bool first) -> hipError_t {
-      return with_acc<T>(first, [&](auto acc) -> hipError_t {
-        constexpr bool ACC = decltype(acc)::value;
-        const auto launch = [&](auto key) {
-          hipLaunchKernelGGL(
-              (k_bwd_dkv_scan<T, bwd_max_m<T>(true), KN, decltype(key)::value, ACC>),
-              dim3(a.nseg * sh.BH), dim3(kScanThreads), 0, st, (const T *)a.Q, (const T *)a.K,
-              (const T *)a.V, (const T *)a.dout, a.aux, (const Mma<T>::frag *)a.wfr, a.bq, a.W,
-              a.state, (T *)a.dK, (T *)a.dV, sh.H, sh.L, a.seg_len, a.nseg, sh.s, sh.Mr,
-              feature_norm(sh), sh.M, m0, wts);
-        };
-        launch(std::false_type{});
-        launch(std::true_type{});
-        return hipGetLastError();
-      });
+    return over_slices(sh, false, [&](int m0, auto acc) -> hipError_t {
+      constexpr bool ACC = decltype(acc)::value;
+      const auto launch = [&](auto key) {
+        hipLaunchKernelGGL((k_bwd_dkv_scan<T, kF32ScanM, KN, decltype(key)::value, ACC>),
+                           dim3(a.nseg * sh.BH), dim3(kScanThreads), 0, st, (const T *)a.Q,
+                           (const T *)a.K, (const T *)a.V, (const T *)a.dout, a.aux,
+                           (const Mma<T>::frag *)a.wfr, a.bq, a.W, a.state, (T *)a.dK,
+                           (T *)a.dV, sh.H, sh.L, a.seg_len, a.nseg, sh.s, sh.Mr,
+                           feature_norm(sh), sh.M, m0, wts);
+      };
+      launch(std::false_type{});
+      launch(std::true_type{});
+      return hipGetLastError();
     });
   });
 }
 
-template <typename T>
-static hipError_t bidir_dkv(const Shape &sh, const BwdArgs &a, hipStream_t st) {
-  const float wts = wt_scale(sh);
+static hipError_t bidir_dkv_bf16(const Shape &sh, const BwdArgs &a, hipStream_t st) {
+  using T = bf16;
+  const int rows = kBwdBidirThreads / 4 * kBwdTbw;
+  const int ntiles = (sh.L + rows - 1) / rows;
+  const int nitems = ntiles * sh.BH;
+  dim3 grid(min(nitems, kBwdMaxWorkgroups));
   return bwd_variant(sh, [&](auto kn, auto) -> hipError_t {
     constexpr int KN = decltype(kn)::value;
-    return over_slices<T>(sh, false, [&](int ms, int m0, bool first) -> hipError_t {
-      return with_acc<T>(first, [&](auto acc) -> hipError_t {
-        constexpr bool ACC = decltype(acc)::value;
-        const int rows = kBwdBidirThreads / 4 * kBwdTbw;
-        const int ntiles = (sh.L + rows - 1) / rows;
-        const int nitems = ntiles * sh.BH;
-        dim3 grid(min(nitems, kBwdMaxWorkgroups));
-        FAVOR_BWD_DISPATCH_M(bwd_max_m<T>(false), ms,
-            hipLaunchKernelGGL((k_bwd_dkv<T, MM, KN, kBwdTbw, ACC>), grid,
-                               dim3(kBwdBidirThreads), 0, st, (const T *)a.K, (const T *)a.V,
-                               (const typename Mma<T>::frag *)a.wfr, a.bq, a.W, a.state,
-                               (T *)a.dK, (T *)a.dV, sh.H, sh.L, sh.s, sh.Mr,
-                               feature_norm(sh), sh.M, m0, wts, ntiles, nitems));
-        return hipGetLastError();
-      });
-    });
+    FAVOR_BWD_DISPATCH_M(sh.M,
+        hipLaunchKernelGGL((k_bwd_dkv<T, MM, KN, kBwdTbw>), grid, dim3(kBwdBidirThreads), 0, st,
+                           (const T *)a.K, (const T *)a.V, (const Mma<T>::frag *)a.wfr, a.bq,
+                           a.W, a.state, (T *)a.dK, (T *)a.dV, sh.H, sh.L, sh.s, sh.Mr,
+                           feature_norm(sh), wt_scale(sh), ntiles, nitems));
+    return hipGetLastError();
   });
 }
 
 hipError_t launch_bwd_dkv(const Shape &sh, Dt in, bool causal, const BwdArgs &a, hipStream_t st) {
   if (causal)
     return in == Dt::BF16 ? launch_bwd_dkv_scan(sh, a, st) : causal_dkv_f32(sh, a, st);
-  return in == Dt::BF16 ? bidir_dkv<bf16>(sh, a, st) : bidir_dkv<float>(sh, a, st);
+  return in == Dt::BF16 ? bidir_dkv_bf16(sh, a, st) : launch_bwd_dkv_f32(sh, a, st);
 }
 
 }  // namespace favor

@@ -126,6 +126,9 @@ hipError_t launch_bwd_dkv(const Shape &sh, Dt in, bool causal, const BwdArgs &a,
 // The causal gradients of bf16 inputs (backward_scan.hip).
 hipError_t launch_bwd_dq_scan(const Shape &sh, const BwdArgs &a, bool accumulate, hipStream_t st);
 hipError_t launch_bwd_dkv_scan(const Shape &sh, const BwdArgs &a, hipStream_t st);
+// The bidirectional gradients of fp32 inputs (backward_f32.hip).
+hipError_t launch_bwd_dq_f32(const Shape &sh, const BwdArgs &a, hipStream_t st);
+hipError_t launch_bwd_dkv_f32(const Shape &sh, const BwdArgs &a, hipStream_t st);
 // Fixed-order sum of split partials [BH][ns][M][65] -> [BH][M][65].
 hipError_t launch_sum_splits(const Shape &sh, const float *part, int ns, float *dst,
                              hipStream_t st);
