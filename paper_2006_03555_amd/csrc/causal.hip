@@ -598,6 +598,23 @@ __device__ __forceinline__ void stage_causal_tile(CausalFsTile<T> &tl, const Til
   }
 }
 
+// A call whose heads are one segment each (nseg = 1) is one launch: the scan
+// builds W'' from W itself, starts from state_in and writes state_out from its
+// state, so neither the key pass nor the segment scan runs. It leaves in the
+// workspace what those launches leave there (W'', b'', the prefix), which a
+// backward call may read. W null: not such a call. (The reordered chunk, which
+// reads W'' from memory again for every chunk, does not take this form: other
+// workgroups of its head would have to wait for the one that writes it.)
+struct CausalSolo {
+  const float *W, *b;
+  const float *state_in;   // [BH][M_r][65], nullable
+  float *state_out;        // nullable
+  bf16x8 *wfr;
+  float *bq, *prefix;
+  float ws, bs, keps;
+  int Mr;
+};
+
 template <typename To, int M, int KN, bool RN, bool SAVE, int T = 64>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 32 ? 2 : 1))) void k_causal_fs(const bf16 *__restrict__ Q,
                                                    const bf16 *__restrict__ K,
@@ -607,7 +624,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 32 ? 2
                                                    const float *__restrict__ prefix,
                                                    To *__restrict__ out, float *__restrict__ rsave,
                                                    int H, int L, int seg_len, int nseg, float s,
-                                                   float eps, float cM) {
+                                                   float eps, float cM, CausalSolo solo) {
   constexpr int MW = M / 4;          // features per wave
   constexpr int MB = MW / 16;        // 16-feature blocks per wave
   constexpr int KS = (MB + 1) / 2;   // 32-feature k-steps per wave (a lone block is zero-padded)
@@ -683,15 +700,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 32 ? 2
       }
     }
   };
-  load_wf();
+  const bool is_solo = !kLate && solo.W != nullptr;
+  if (is_solo) {
+    const float *Wh = solo.W + (size_t)h * solo.Mr * kD;
+    const float *bh_ = solo.b + (size_t)h * solo.Mr;
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int mbg = w * MB + mb;
-    const float *bb = bqg + (size_t)h * M + 16 * mbg;
-    if constexpr (!kLate) {
-      bk[mb] = bb[c16];
+    for (int mb = 0; mb < MB; ++mb) {
+      const int m = 16 * (w * MB + mb) + c16;
+      const float *row = Wh + (size_t)min(m, solo.Mr - 1) * kD + 8 * g;
+      const float sc = m < solo.Mr ? solo.ws : 0.f;   // rows past the M_r drawn are zero
 #pragma unroll
-      for (int j = 0; j < 4; ++j) bqv[mb][j] = bb[4 * g + j];
+      for (int k = 0; k < 2; ++k) {
+        float v[8];
+        load8_f32(row + 32 * k, v);
+        wf[mb][k] = m < solo.Mr ? P::from_f32(v, sc) : P::splat(0.f);
+      }
+      bk[mb] = seed_row<KN>(m, solo.Mr, bh_, solo.bs, solo.keps);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        bqv[mb][j] = seed_row<KN>(16 * (w * MB + mb) + 4 * g + j, solo.Mr, bh_, solo.bs, solo.keps);
+      if (bh < H) {
+        frag *dst = solo.wfr + ((size_t)h * (M / 16) + w * MB + mb) * 2 * 64 + l;
+        dst[0] = wf[mb][0];
+        dst[64] = wf[mb][1];
+        if (g == 0) solo.bq[(size_t)h * M + m] = bk[mb];
+      }
+    }
+  } else {
+    load_wf();
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const int mbg = w * MB + mb;
+      const float *bb = bqg + (size_t)h * M + 16 * mbg;
+      if constexpr (!kLate) {
+        bk[mb] = bb[c16];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bqv[mb][j] = bb[4 * g + j];
+      }
     }
   }
   if (kLate && tid < M) sm.bq[tid] = bqg[(size_t)h * M + tid];
@@ -713,7 +758,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 32 ? 2
   // state rows m = w MW + 16 mb + 4 g + j, lane column c16 of block nb holding
   // value column pi(nb, c16) (block 4: the ones column in all 16 columns)
   f32x4 accS[MB][5];
-  {
+  // one segment: the state crosses LDS (the hand-over area, free outside the
+  // chunks) so that global memory is read and written in whole lines
+  f32x4 *const st4 = reinterpret_cast<f32x4 *>(&sm.num[0][0][0][0][0]);
+  float *const st1 = reinterpret_cast<float *>(st4);
+  static_assert(kLate || sizeof(sm.num) >= (size_t)M * 65 * sizeof(float), "state staging");
+  constexpr int kStateQuads = M * 65 / 4;
+  if (is_solo) {
+    const int drawn = solo.state_in ? solo.Mr * 65 / 4 : 0;   // padding rows hold no state
+    const f32x4 *src = reinterpret_cast<const f32x4 *>(solo.state_in) + (size_t)bh * (solo.Mr * 65 / 4);
+    f32x4 *dst = reinterpret_cast<f32x4 *>(solo.prefix) + (size_t)bh * kStateQuads;
+    constexpr int IT = (kStateQuads + 255) / 256;
+    f32x4 v[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int i = it * 256 + tid;
+      v[it] = zero4;
+      if (i < drawn) v[it] = src[i];
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int i = it * 256 + tid;
+      if (i < kStateQuads) {
+        st4[i] = v[it];
+        dst[i] = v[it];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float *row = st1 + (w * MW + mb * 16 + 4 * g + j) * 65;
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) accS[mb][nb][j] = row[perm_col(nb, c16)];
+        accS[mb][4][j] = row[64];
+      }
+  } else {
     const float *pre = prefix + ((size_t)bh * nseg + seg) * M * 65;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -1103,6 +1184,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 32 ? 2
   }
   // the last chunk
   if (r1 > r0) finalize(r0 + T * ((r1 - r0 - 1) / T), buf ^ 1);
+  if (is_solo && solo.state_out) {   // the state after the last token
+    __syncthreads();   // the hand-over area's last readers
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float *row = st1 + (w * MW + mb * 16 + 4 * g + j) * 65;
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) row[perm_col(nb, c16)] = accS[mb][nb][j];
+        if (c16 == 0) row[64] = accS[mb][4][j];
+      }
+    __syncthreads();
+    const int quads = solo.Mr * 65 / 4;
+    f32x4 *dst = reinterpret_cast<f32x4 *>(solo.state_out) + (size_t)bh * quads;
+    for (int i = tid; i < quads; i += 256) dst[i] = st4[i];
+  }
 }
 
 hipError_t launch_seg_scan(const Shape &sh, Dt in, float *part, int nseg, const float *state_in,
@@ -1130,7 +1227,8 @@ static hipError_t with_variant(const Shape &sh, F &&f) {
 template <typename To, bool SAVE = false>
 static hipError_t causal_fs_typed(const Shape &sh, const void *Q, const void *K, const void *V,
                                   const void *wfr, const float *bq, const float *prefix, void *o,
-                                  int seg_len, int nseg, hipStream_t st, float *rsave = nullptr) {
+                                  int seg_len, int nseg, hipStream_t st, float *rsave = nullptr,
+                                  const CausalSolo &solo = CausalSolo{}) {
   dim3 grid(nseg * sh.BH);
   return with_variant(sh, [&](auto kn, auto rn) -> hipError_t {
     constexpr int KN = decltype(kn)::value;
@@ -1142,7 +1240,7 @@ static hipError_t causal_fs_typed(const Shape &sh, const void *Q, const void *K,
   hipLaunchKernelGGL((k_causal_fs<To, MM, KN, RN, SAVE, TT>), grid, dim3(256), 0, st,         \
                      (const bf16 *)Q, (const bf16 *)K, (const bf16 *)V, (const bf16x8 *)wfr,   \
                      bq, prefix, (To *)o, rsave, sh.H, sh.L, seg_len, nseg, sh.s, sh.eps,      \
-                     feature_norm(sh))
+                     feature_norm(sh), solo)
 #define FAVOR_CAUSAL_FS_M(TT)                                                                \
   switch (sh.M) {                                                                           \
     case 64: FAVOR_CAUSAL_FS_LAUNCH(64, TT); break;                                          \
@@ -1222,6 +1320,25 @@ hipError_t launch_causal(const Shape &sh, Dt in, Dt out, const void *Q, const vo
                                                      nseg, st, halves)
                          : causal_typed<float, float>(sh, Q, K, V, wfr, bq, prefix, o, seg_len,
                                                       nseg, st, halves);
+}
+
+bool causal_solo(const Shape &sh, Dt in, int nseg) {
+  return nseg == 1 && in == Dt::BF16 && !(sh.chunk == 32 && sh.M > 128);
+}
+
+hipError_t launch_causal_solo(const Shape &sh, Dt out, const void *Q, const void *K,
+                              const void *V, const float *W, const float *b, void *wfr,
+                              float *bq, float *prefix, void *o, const float *state_in,
+                              float *state_out, float *rsave, int seg_len, hipStream_t st) {
+  CausalSolo solo{W, b, state_in, state_out, (bf16x8 *)wfr, bq, prefix, 0.f, 0.f, sh.keps, sh.Mr};
+  feature_scales(sh, solo.ws, solo.bs);
+  if (rsave)
+    return causal_fs_typed<bf16, true>(sh, Q, K, V, wfr, bq, prefix, o, seg_len, 1, st, rsave,
+                                       solo);
+  return out == Dt::BF16
+             ? causal_fs_typed<bf16>(sh, Q, K, V, wfr, bq, prefix, o, seg_len, 1, st, nullptr, solo)
+             : causal_fs_typed<float>(sh, Q, K, V, wfr, bq, prefix, o, seg_len, 1, st, nullptr,
+                                      solo);
 }
 
 }  // namespace favor

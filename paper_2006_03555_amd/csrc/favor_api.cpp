@@ -508,6 +508,15 @@ favor_status favor_attn_causal_save(const favor_desc *g, const void *Q, const vo
   float *bq = f.bq;
   float *halves = f.halves;
   hipError_t e;
+  if (favor::causal_solo(sh, in, p.nsplit)) {
+    {
+      favor::LaunchTimer t(favor::kKerCausal, st);
+      e = favor::launch_causal_solo(sh, dt_of(g->out_dtype), Q, K, V, W, b, wfr, bq, part, out,
+                                    state_in, state_out, sh.renorm ? row_scale : nullptr,
+                                    p.rows_per_split, st);
+    }
+    return device_result(e, "favor_attn_causal chunk scan");
+  }
   {
     favor::LaunchTimer t(favor::kKerKside, st);
     e = favor::launch_kside(sh, in, K, V, W, b, wfr, bq, part, p.rows_per_split, p.nsplit, st);

@@ -137,6 +137,18 @@ hipError_t launch_sum_splits(const Shape &sh, const float *part, int ns, float *
 hipError_t launch_suffix_scan(const Shape &sh, float *part, int nch, const float *dsout,
                               float *dsin, hipStream_t st, const float *bias = nullptr);
 
+// A causal call of one segment per head as one launch (bf16): the scan builds W''
+// itself, starts from state_in (nullable), writes state_out (nullable) and leaves
+// W'', b'' and the prefix in the workspace. causal_solo: whether a call takes
+// this form. With one segment the key pass and the segment scan produce nothing
+// but state_out, which the scan's own state is. B1 H8 L128 M256 with a carried
+// state: 25.4 us in three launches, 17.9 us in one.
+bool causal_solo(const Shape &sh, Dt in, int nseg);
+hipError_t launch_causal_solo(const Shape &sh, Dt out, const void *Q, const void *K,
+                              const void *V, const float *W, const float *b, void *wfr,
+                              float *bq, float *prefix, void *o, const float *state_in,
+                              float *state_out, float *rsave, int seg_len, hipStream_t st);
+
 // Causal chunk scan of each segment starting from its prefix state. halves:
 // [BH][L][68] fp32 scratch for fp32 inputs at M = 256 (two feature-half
 // passes), else unused (may be null).

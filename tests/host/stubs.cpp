@@ -102,6 +102,18 @@ hipError_t launch_causal(const Shape &sh, Dt, Dt, const void *Q, const void *K, 
   require(Q && K && V && wfr && bq && prefix && o, "causal pass pointers");
   return ran();
 }
+bool causal_solo(const Shape &sh, Dt in, int nseg) {
+  return nseg == 1 && in == Dt::BF16 && !(sh.chunk == 32 && sh.M > 128);
+}
+hipError_t launch_causal_solo(const Shape &sh, Dt, const void *Q, const void *K, const void *V,
+                              const float *W, const float *b, void *wfr, float *bq,
+                              float *prefix, void *o, const float *, float *, float *,
+                              int seg_len, hipStream_t) {
+  shape_ok(sh);
+  plan_ok(sh, seg_len, 1);
+  require(Q && K && V && W && b && wfr && bq && prefix && o, "one-segment causal pass pointers");
+  return ran();
+}
 hipError_t launch_kside_agg(const Shape &sh, Dt, const void *Q, const void *dout, const float *W,
                             const float *b, const float2 *aux, float *part, int rows,
                             int nsplit, hipStream_t) {

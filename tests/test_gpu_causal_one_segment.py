@@ -1,0 +1,78 @@
+"""Causal calls whose heads are one segment each (bf16): one launch that builds
+W'' itself and carries the state. Against the oracle, with the state in place,
+and with a backward call reading the workspace it leaves."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from helpers import TOL, parity, to_dev, to_host
+from oracle import favor
+
+pytestmark = pytest.mark.gpu
+
+S64 = 64 ** -0.25
+
+
+# one chunk and less, whole and ragged chunks; one segment by length, by
+# descriptor (segment >= L) or by head count (more heads than CUs)
+@pytest.mark.parametrize("B,H,L,segment", [(1, 2, 1, 0), (2, 2, 63, 0), (1, 3, 128, 0),
+                                           (1, 2, 191, 0), (1, 2, 700, 704), (33, 8, 300, 0)])
+@pytest.mark.parametrize("M,chunk", [(64, 0), (112, 64), (128, 0), (208, 64), (256, 0), (256, 32)])
+@pytest.mark.parametrize("kernel", ["softmax", "relu"])
+@pytest.mark.parametrize("state", [False, True])
+def test_one_segment(B, H, L, segment, M, chunk, kernel, state):
+    import torch
+    fv = __import__("paper_2006_03555_amd")
+    if B > 30 and (M, state) not in ((256, True), (112, False)):
+        pytest.skip("many heads are run on two of the combinations")
+    kn = favor.KERNEL_RELU if kernel == "relu" else favor.KERNEL_SOFTMAX
+    Q, K, V = wl.make_qkv(wl.Workload("t", "causal", B, H, L, 64, M, "bf16", M + L))
+    W, b = favor.orf_draw(23, H, M, 64)
+    W, b = W.astype(np.float32), b.astype(np.float32)
+    S0 = None
+    if state:
+        Qe, Ke, Ve = wl.make_qkv(wl.Workload("t", "causal", B, H, 256, 64, M, "bf16", 9))
+        _, S0 = favor.attn_causal(Qe, Ke, Ve, W, b, S64, kernel=kn)
+        S0 = S0.astype(np.float32)
+    q, k, v = (to_dev(x, "bf16") for x in (Q, K, V))
+    Wd, bd = to_dev(W), to_dev(b)
+    s = to_dev(S0) if state else None
+    kw = dict(kernel=kn, segment=segment, chunk=chunk)
+    out, s1 = fv.attn_causal(q, k, v, Wd, bd, S64, state_in=s, return_state=True, **kw)
+    heads = [(0, 0), (B - 1, H - 1)]
+    stats = {}
+    # cos features at M = 64: the first rows' denominators may cancel
+    parity(to_host(out), Q, K, V, W, b, S64, True, "bf16", state_in=S0, heads=heads, kernel=kn,
+           gate="cond" if M == 64 and kernel == "softmax" else "both", stats=stats)
+    Kp = favor.features(K[-1:, -1:], W[-1:], b[-1:], S64, kn)
+    C = np.concatenate([V[-1:, -1:], np.ones_like(V[-1:, -1:, :, :1])], -1).astype(np.float64)
+    ref = np.swapaxes(Kp, -1, -2) @ C + (S0[-1, -1].astype(np.float64) if state else 0.0)
+    got = to_host(s1)[-1:, -1:]
+    assert np.max(np.abs(got - ref)) <= TOL["bf16"] * np.max(np.abs(ref))
+    if state:   # the state updated in place
+        out2, s2 = fv.attn_causal(q, k, v, Wd, bd, S64, state_in=s, state_out=s,
+                                  return_state=True, **kw)
+        assert torch.equal(out2, out) and torch.equal(s2, s1)
+
+
+@pytest.mark.parametrize("M", [64, 112, 256])
+def test_backward_reads_its_workspace(M):
+    import torch
+    fv = __import__("paper_2006_03555_amd")
+    B, H, L = 2, 2, 150
+    Q, K, V = wl.make_qkv(wl.Workload("t", "causal", B, H, L, 64, M, "bf16", 4))
+    W, b = favor.orf_draw(24, H, M, 64)
+    q, k, v = (to_dev(x, "bf16") for x in (Q, K, V))
+    Wd, bd = to_dev(W), to_dev(b)
+    do = to_dev(np.random.default_rng(1).standard_normal((B, H, L, 64)), "bf16")
+    _, s0 = fv.attn_causal(k, q, v, Wd, bd, S64, return_state=True)
+    g = fv.make_desc(B, H, L, 64, M, fv.BF16, fv.BF16, S64)
+    ws = torch.full((fv.workspace_size(g, 1),), 255, dtype=torch.uint8, device="cuda")
+    rs = torch.empty((B, H, L), device="cuda")
+    out = fv.attn_causal(q, k, v, Wd, bd, S64, state_in=s0, workspace=ws, row_scale=rs)
+    a = fv.attn_causal_backward(q, k, v, Wd, bd, S64, do, state_in=s0, return_state_grad=True,
+                                out=out, row_scale=rs, forward_workspace=ws,
+                                forward_call="causal")
+    c = fv.attn_causal_backward(q, k, v, Wd, bd, S64, do, state_in=s0, return_state_grad=True,
+                                out=out, row_scale=rs)
+    assert all(torch.equal(x, y) for x, y in zip(a, c))
