@@ -18,6 +18,7 @@ calls take row_scale (a [B, H, L] float32 tensor) to save each row's
 """
 import ctypes
 import functools
+import operator
 import os
 
 from ._lib import (  # noqa: F401
@@ -36,9 +37,15 @@ __all__ = [
 ]
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _dtype_code(t):
@@ -56,9 +63,16 @@ def _torch_dtype(code):
 
 
 def _stream(stream):
+    """HIP stream handle of `stream`, or of the current device's current stream (the
+    raw handle where torch offers it: building a Stream object costs microseconds
+    of every call)."""
+    if stream is not None:
+        return stream.cuda_stream
     torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _on_stream(fn):
@@ -71,7 +85,9 @@ def _on_stream(fn):
     def wrapper(*args, stream=None, **kw):
         # entering a stream context costs microseconds of host time per call:
         # skip it when the caller's stream already is the current one
-        if stream is None or stream == _torch().cuda.current_stream():
+        if stream is None:
+            return fn(*args, **kw)
+        if stream == _torch().cuda.current_stream():
             return fn(*args, stream=stream, **kw)
         with _torch().cuda.stream(stream):
             return fn(*args, stream=stream, **kw)
@@ -79,7 +95,8 @@ def _on_stream(fn):
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    """Address of a tensor, NULL for None (the ctypes signatures take both)."""
+    return None if t is None else t.data_ptr()
 
 
 def _check(status):
@@ -89,7 +106,7 @@ def _check(status):
 
 def _require_cuda(*ts):
     for t in ts:
-        if t is not None and (not t.is_cuda or not t.is_contiguous()):
+        if t is not None and not (t.is_cuda and t.is_contiguous()):
             raise FavorError(1, "tensors must be contiguous GPU tensors")
 
 
@@ -115,7 +132,7 @@ def _require_like(t, shape, dtype, name):
     writes or reads (the kernels trust the descriptor, not the tensor)."""
     if t is None:
         return
-    if tuple(t.shape) != tuple(shape) or t.dtype != dtype:
+    if t.shape != shape or t.dtype != dtype:   # torch.Size compares as a tuple
         raise FavorError(1, f"{name} must be {tuple(shape)} {dtype}, got {tuple(t.shape)} "
                             f"{t.dtype}")
 
@@ -126,25 +143,60 @@ def _require_features(W, b, H, M, d):
     _require_like(b, (H, M), torch.float32, "b")
 
 
-def _desc_for(X, W, input_scale, out_dtype, denom_eps=0.0, segment=0, others=(), opts=None):
-    """Descriptor for inputs X [B, H, L, d] (and tensors `others` of the same shape
+class _Call:
+    """A descriptor with its by-reference argument and the workspace sizes asked
+    for so far. Held by value (see _call_for), read-only once built."""
+    __slots__ = ("g", "ref", "B", "H", "L", "d", "M", "out_code", "sizes")
+
+    def __init__(self, g):
+        self.g = g
+        self.ref = ctypes.byref(g)
+        self.B, self.H, self.L, self.d, self.M = g.B, g.H, g.L, g.d, g.M
+        self.out_code = g.out_dtype
+        self.sizes = {}
+
+    def workspace(self, op):
+        n = self.sizes.get(op)
+        if n is None:
+            n = self.sizes[op] = workspace_size(self.g, op)
+        return n
+
+    def backward_workspace(self, op):
+        n = self.sizes.get(("backward", op))
+        if n is None:
+            n = self.sizes[("backward", op)] = backward_workspace_size(self.g, op)
+        return n
+
+
+@functools.lru_cache(maxsize=256)
+def _call_for(B, H, L, d, M, in_code, out_code, input_scale, denom_eps, segment, kernel,
+              renormalize, kernel_eps, chunk):
+    """The _Call of these values. Building the descriptor and asking the library for
+    the workspace size cost several microseconds of every call of a program that
+    makes the same one again; every argument is a plain number, so an entry depends
+    on nothing else."""
+    return _Call(make_desc(B, H, L, d, M, in_code, out_code, input_scale, denom_eps, segment,
+                           kernel=kernel, renormalize=renormalize, kernel_eps=kernel_eps,
+                           chunk=chunk))
+
+
+def _desc_for(X, W, input_scale, out_dtype, denom_eps=0.0, segment=0, others=(),
+              kernel=KERNEL_SOFTMAX, renormalize=True, kernel_eps=1e-3, chunk=0):
+    """_Call for inputs X [B, H, L, d] (and tensors `others` of the same shape
     and dtype) with features W [H, M, d], b [H, M]."""
     if X.dim() != 4:
         raise FavorError(1, f"inputs must be [B, H, L, d], got {tuple(X.shape)}")
-    B, H, L, d = X.shape
+    shape, dtype = X.shape, X.dtype
+    B, H, L, d = shape
     for name, t in others:
-        _require_like(t, X.shape, X.dtype, name)
+        _require_like(t, shape, dtype, name)
     if W.dim() != 3:
         raise FavorError(1, f"W must be [H, M, d], got {tuple(W.shape)}")
-    M = W.shape[1]
-    in_code = _dtype_code(X.dtype)
+    in_code = _dtype_code(dtype)
     out_code = in_code if out_dtype is None else _dtype_code(out_dtype)
-    return make_desc(B, H, L, d, M, in_code, out_code, input_scale, denom_eps, segment,
-                     **(opts or {}))
-
-
-def _opts(kernel, renormalize, kernel_eps):
-    return dict(kernel=kernel, renormalize=renormalize, kernel_eps=kernel_eps)
+    return _call_for(B, H, L, d, W.shape[1], in_code, out_code, float(input_scale),
+                     float(denom_eps), operator.index(segment), int(kernel), bool(renormalize),
+                     float(kernel_eps), operator.index(chunk))
 
 
 def _out_dtype(out_dtype, out, X):
@@ -160,25 +212,29 @@ def feature_map(X, W, b, input_scale, out_dtype=None, out=None, stream=None,
     """X' [B, H, L, M] (favor_feature_map): D_X X-hat, or the ReLU features."""
     torch = _torch()
     g = _desc_for(X, W, input_scale, _out_dtype(out_dtype, out, X),
-                  opts=_opts(kernel, True, kernel_eps))
+                  kernel=kernel, kernel_eps=kernel_eps)
     _require_features(W, b, g.H, g.M, g.d)
     shape = (g.B, g.H, g.L, g.M)
     if out is None:
-        out = torch.empty(shape, dtype=_torch_dtype(g.out_dtype), device=X.device)
-    _require_like(out, shape, _torch_dtype(g.out_dtype), "out")
+        out = torch.empty(shape, dtype=_torch_dtype(g.out_code), device=X.device)
+    _require_like(out, shape, _torch_dtype(g.out_code), "out")
     _require_cuda(X, W, b, out)
-    _check(lib().favor_feature_map(ctypes.byref(g), _ptr(X), _ptr(W), _ptr(b), _ptr(out),
+    _check(lib().favor_feature_map(g.ref, _ptr(X), _ptr(W), _ptr(b), _ptr(out),
                                    _stream(stream)))
     return out
 
 
 def _workspace(g, causal, workspace):
+    return _workspace_of(g.workspace(causal), workspace)
+
+
+def _workspace_of(n, workspace):
     torch = _torch()
-    n = workspace_size(g, causal)
-    if workspace is None:
-        workspace = torch.empty(max(n, 1), dtype=torch.uint8,
-                                device=torch.device("cuda", torch.cuda.current_device()))
-    return workspace, workspace.numel() * workspace.element_size()
+    if workspace is not None:
+        return workspace, workspace.numel() * workspace.element_size()
+    n = max(n, 1)
+    return torch.empty(n, dtype=torch.uint8,
+                       device=torch.device("cuda", torch.cuda.current_device())), n
 
 
 def _require_row_scale(t, g, name):
@@ -193,22 +249,23 @@ def attn_bidir(Q, K, V, W, b, input_scale, denom_eps=0.0, out_dtype=None, out=No
     """Bidirectional FAVOR, Algorithm 1 (favor_attn_bidir). Returns out [B, H, L, d]."""
     torch = _torch()
     g = _desc_for(Q, W, input_scale, _out_dtype(out_dtype, out, Q), denom_eps,
-                  others=(("K", K), ("V", V)), opts=_opts(kernel, renormalize, kernel_eps))
+                  others=(("K", K), ("V", V)), kernel=kernel, renormalize=renormalize,
+                  kernel_eps=kernel_eps)
     _require_features(W, b, g.H, g.M, g.d)
     if out is None:
-        out = torch.empty(Q.shape, dtype=_torch_dtype(g.out_dtype), device=Q.device)
-    _require_like(out, Q.shape, _torch_dtype(g.out_dtype), "out")
+        out = torch.empty(Q.shape, dtype=_torch_dtype(g.out_code), device=Q.device)
+    _require_like(out, Q.shape, _torch_dtype(g.out_code), "out")
     _require_row_scale(row_scale, g, "row_scale")
     _require_cuda(Q, K, V, W, b, out, row_scale)
     ws, nbytes = _workspace(g, 0, workspace)
     if row_scale is None:
-        _check(lib().favor_attn_bidir(ctypes.byref(g), _ptr(Q), _ptr(K), _ptr(V), _ptr(W),
-                                      _ptr(b), _ptr(out), _ptr(ws), ctypes.c_size_t(nbytes),
+        _check(lib().favor_attn_bidir(g.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(W),
+                                      _ptr(b), _ptr(out), _ptr(ws), nbytes,
                                       _stream(stream)))
     else:
-        _check(lib().favor_attn_bidir_save(ctypes.byref(g), _ptr(Q), _ptr(K), _ptr(V), _ptr(W),
+        _check(lib().favor_attn_bidir_save(g.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(W),
                                            _ptr(b), _ptr(out), _ptr(row_scale), _ptr(ws),
-                                           ctypes.c_size_t(nbytes), _stream(stream)))
+                                           nbytes, _stream(stream)))
     return out
 
 
@@ -226,27 +283,27 @@ def attn_causal(Q, K, V, W, b, input_scale, denom_eps=0.0, state_in=None, return
     torch = _torch()
     g = _desc_for(Q, W, input_scale, _out_dtype(out_dtype, out, Q), denom_eps, segment,
                   others=(("K", K), ("V", V)),
-                  opts=dict(_opts(kernel, renormalize, kernel_eps), chunk=chunk))
+                  kernel=kernel, renormalize=renormalize, kernel_eps=kernel_eps, chunk=chunk)
     _require_features(W, b, g.H, g.M, g.d)
     sshape = (g.B, g.H, g.M, g.d + 1)
     if out is None:
-        out = torch.empty(Q.shape, dtype=_torch_dtype(g.out_dtype), device=Q.device)
+        out = torch.empty(Q.shape, dtype=_torch_dtype(g.out_code), device=Q.device)
     if return_state and state_out is None:
         state_out = torch.empty(sshape, dtype=torch.float32, device=Q.device)
-    _require_like(out, Q.shape, _torch_dtype(g.out_dtype), "out")
+    _require_like(out, Q.shape, _torch_dtype(g.out_code), "out")
     _require_like(state_in, sshape, torch.float32, "state_in")
     _require_like(state_out, sshape, torch.float32, "state_out")
     _require_row_scale(row_scale, g, "row_scale")
     _require_cuda(Q, K, V, W, b, out, state_in, state_out, row_scale)
     ws, nbytes = _workspace(g, 1, workspace)
     if row_scale is None:
-        _check(lib().favor_attn_causal(ctypes.byref(g), _ptr(Q), _ptr(K), _ptr(V), _ptr(W),
+        _check(lib().favor_attn_causal(g.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(W),
                                        _ptr(b), _ptr(out), _ptr(state_in), _ptr(state_out),
-                                       _ptr(ws), ctypes.c_size_t(nbytes), _stream(stream)))
+                                       _ptr(ws), nbytes, _stream(stream)))
     else:
-        _check(lib().favor_attn_causal_save(ctypes.byref(g), _ptr(Q), _ptr(K), _ptr(V), _ptr(W),
+        _check(lib().favor_attn_causal_save(g.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(W),
                                             _ptr(b), _ptr(out), _ptr(state_in), _ptr(state_out),
-                                            _ptr(row_scale), _ptr(ws), ctypes.c_size_t(nbytes),
+                                            _ptr(row_scale), _ptr(ws), nbytes,
                                             _stream(stream)))
     return (out, state_out) if return_state else out
 
@@ -264,9 +321,9 @@ def attn_both(Q, K, V, W, b, input_scale, denom_eps=0.0, state_in=None, return_s
     torch = _torch()
     g = _desc_for(Q, W, input_scale, _out_dtype(out_dtype, out_bidir, Q), denom_eps, segment,
                   others=(("K", K), ("V", V)),
-                  opts=dict(_opts(kernel, renormalize, kernel_eps), chunk=chunk))
+                  kernel=kernel, renormalize=renormalize, kernel_eps=kernel_eps, chunk=chunk)
     _require_features(W, b, g.H, g.M, g.d)
-    odt = _torch_dtype(g.out_dtype)
+    odt = _torch_dtype(g.out_code)
     sshape = (g.B, g.H, g.M, g.d + 1)
     if out_bidir is None:
         out_bidir = torch.empty(Q.shape, dtype=odt, device=Q.device)
@@ -283,10 +340,10 @@ def attn_both(Q, K, V, W, b, input_scale, denom_eps=0.0, state_in=None, return_s
     _require_cuda(Q, K, V, W, b, out_bidir, out_causal, state_in, state_out, row_scale_bidir,
                   row_scale_causal)
     ws, nbytes = _workspace(g, 2, workspace)
-    _check(lib().favor_attn_both(ctypes.byref(g), _ptr(Q), _ptr(K), _ptr(V), _ptr(W), _ptr(b),
+    _check(lib().favor_attn_both(g.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(W), _ptr(b),
                                  _ptr(out_bidir), _ptr(out_causal), _ptr(state_in),
                                  _ptr(state_out), _ptr(row_scale_bidir), _ptr(row_scale_causal),
-                                 _ptr(ws), ctypes.c_size_t(nbytes), _stream(stream)))
+                                 _ptr(ws), nbytes, _stream(stream)))
     if return_state:
         return out_bidir, out_causal, state_out
     return out_bidir, out_causal
@@ -304,9 +361,9 @@ def attn_both_noalloc(Q, K, V, W, b, input_scale, denom_eps=0.0, state_in=None,
     odt = out_bidir.dtype if out_bidir is not None else Q.dtype
     g = _desc_for(Q, W, input_scale, odt, denom_eps, segment,
                   others=(("K", K), ("V", V)),
-                  opts=dict(_opts(kernel, renormalize, kernel_eps), chunk=chunk))
+                  kernel=kernel, renormalize=renormalize, kernel_eps=kernel_eps, chunk=chunk)
     _require_features(W, b, g.H, g.M, g.d)
-    tdt = _torch_dtype(g.out_dtype)
+    tdt = _torch_dtype(g.out_code)
     sshape = (g.B, g.H, g.M, g.d + 1)
     if out_bidir is None:
         out_bidir = torch.empty(Q.shape, dtype=tdt, device=Q.device)
@@ -321,7 +378,7 @@ def attn_both_noalloc(Q, K, V, W, b, input_scale, denom_eps=0.0, state_in=None,
     _require_cuda(Q, K, V, W, b, out_bidir, out_causal, state_in, state_out, row_scale_bidir,
                   row_scale_causal)
     _check(lib().favor_attn_both_noalloc(
-        ctypes.byref(g), _ptr(Q), _ptr(K), _ptr(V), _ptr(W), _ptr(b), _ptr(out_bidir),
+        g.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(W), _ptr(b), _ptr(out_bidir),
         _ptr(out_causal), _ptr(state_in), _ptr(state_out), _ptr(row_scale_bidir),
         _ptr(row_scale_causal), _stream(stream)))
     return out_bidir, out_causal
@@ -333,12 +390,7 @@ def noalloc_scratch_bytes():
 
 
 def _bwd_workspace(g, causal, workspace):
-    torch = _torch()
-    n = backward_workspace_size(g, causal)
-    if workspace is None:
-        workspace = torch.empty(max(n, 1), dtype=torch.uint8,
-                                device=torch.device("cuda", torch.cuda.current_device()))
-    return workspace, workspace.numel() * workspace.element_size()
+    return _workspace_of(g.backward_workspace(causal), workspace)
 
 
 def _bwd_grads(Q, dQ, dK, dV):
@@ -360,7 +412,7 @@ def _forward_ws(forward_workspace, forward_call, allowed):
     if forward_workspace is None:
         if forward_call is not None:
             raise FavorError(1, "forward_call without forward_workspace")
-        return ctypes.c_void_p(0), 0
+        return None, 0
     if forward_call not in allowed:
         raise FavorError(1, f"forward_call must be one of {sorted(allowed)}, got {forward_call!r}")
     _require_cuda(forward_workspace)
@@ -387,17 +439,18 @@ def attn_bidir_backward(Q, K, V, W, b, input_scale, dout, denom_eps=0.0, dQ=None
     inputs, spares recomputing Buf1."""
     g = _desc_for(Q, W, input_scale, Q.dtype, denom_eps,
                   others=(("K", K), ("V", V), ("dout", dout)),
-                  opts=_opts(kernel, renormalize, kernel_eps))
+                  kernel=kernel, renormalize=renormalize,
+                  kernel_eps=kernel_eps)
     _require_features(W, b, g.H, g.M, g.d)
     dQ, dK, dV = _bwd_grads(Q, dQ, dK, dV)
     _saved(out, row_scale, g, Q)
     _require_cuda(Q, K, V, W, b, dout, dQ, dK, dV, out, row_scale)
     fptr, fop = _forward_ws(forward_workspace, forward_call, ("bidir", "both"))
     ws, nbytes = _bwd_workspace(g, False, workspace)
-    _check(lib().favor_attn_bidir_backward(ctypes.byref(g), _ptr(Q), _ptr(K), _ptr(V), _ptr(W),
+    _check(lib().favor_attn_bidir_backward(g.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(W),
                                            _ptr(b), _ptr(dout), _ptr(out), _ptr(row_scale),
                                            fptr, fop, _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(ws),
-                                           ctypes.c_size_t(nbytes), _stream(stream)))
+                                           nbytes, _stream(stream)))
     return dQ, dK, dV
 
 
@@ -416,7 +469,7 @@ def attn_causal_backward(Q, K, V, W, b, input_scale, dout, denom_eps=0.0, state_
     torch = _torch()
     g = _desc_for(Q, W, input_scale, Q.dtype, denom_eps,
                   others=(("K", K), ("V", V), ("dout", dout)),
-                  opts=dict(_opts(kernel, renormalize, kernel_eps), chunk=chunk))
+                  kernel=kernel, renormalize=renormalize, kernel_eps=kernel_eps, chunk=chunk)
     _require_features(W, b, g.H, g.M, g.d)
     dQ, dK, dV = _bwd_grads(Q, dQ, dK, dV)
     sshape = (g.B, g.H, g.M, g.d + 1)
@@ -430,9 +483,9 @@ def attn_causal_backward(Q, K, V, W, b, input_scale, dout, denom_eps=0.0, state_
     fptr, fop = _forward_ws(forward_workspace, forward_call, ("causal", "both"))
     ws, nbytes = _bwd_workspace(g, True, workspace)
     _check(lib().favor_attn_causal_backward(
-        ctypes.byref(g), _ptr(Q), _ptr(K), _ptr(V), _ptr(W), _ptr(b), _ptr(state_in), _ptr(dout),
+        g.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(W), _ptr(b), _ptr(state_in), _ptr(dout),
         _ptr(out), _ptr(row_scale), fptr, fop, _ptr(dstate_out), _ptr(dQ), _ptr(dK), _ptr(dV),
-        _ptr(dstate_in), _ptr(ws), ctypes.c_size_t(nbytes), _stream(stream)))
+        _ptr(dstate_in), _ptr(ws), nbytes, _stream(stream)))
     return (dQ, dK, dV, dstate_in) if return_state_grad else (dQ, dK, dV)
 
 
@@ -454,7 +507,7 @@ def attn_both_backward(Q, K, V, W, b, input_scale, dout_bidir, dout_causal, deno
     g = _desc_for(Q, W, input_scale, Q.dtype, denom_eps, segment,
                   others=(("K", K), ("V", V), ("dout_bidir", dout_bidir),
                           ("dout_causal", dout_causal)),
-                  opts=dict(_opts(kernel, renormalize, kernel_eps), chunk=chunk))
+                  kernel=kernel, renormalize=renormalize, kernel_eps=kernel_eps, chunk=chunk)
     _require_features(W, b, g.H, g.M, g.d)
     dQ, dK, dV = _bwd_grads(Q, dQ, dK, dV)
     sshape = (g.B, g.H, g.M, g.d + 1)
@@ -469,10 +522,10 @@ def attn_both_backward(Q, K, V, W, b, input_scale, dout_bidir, dout_causal, deno
     fptr, fop = _forward_ws(forward_workspace, forward_call, ("both",))
     ws, nbytes = _bwd_workspace(g, 2, workspace)
     _check(lib().favor_attn_both_backward(
-        ctypes.byref(g), _ptr(Q), _ptr(K), _ptr(V), _ptr(W), _ptr(b), _ptr(state_in),
+        g.ref, _ptr(Q), _ptr(K), _ptr(V), _ptr(W), _ptr(b), _ptr(state_in),
         _ptr(dout_bidir), _ptr(dout_causal), _ptr(out_bidir), _ptr(row_scale_bidir),
         _ptr(out_causal), _ptr(row_scale_causal), fptr, fop, _ptr(dstate_out), _ptr(dQ),
-        _ptr(dK), _ptr(dV), _ptr(dstate_in), _ptr(ws), ctypes.c_size_t(nbytes),
+        _ptr(dK), _ptr(dV), _ptr(dstate_in), _ptr(ws), nbytes,
         _stream(stream)))
     return (dQ, dK, dV, dstate_in) if return_state_grad else (dQ, dK, dV)
 
