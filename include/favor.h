@@ -89,8 +89,9 @@ typedef struct {
   int32_t chunk;            /* causal chunk length T: tokens per step of the
                                prefix-sum scan (Sec. 2.5.1): 64 (four 16-token
                                matrix-core blocks in the intra-chunk product) or,
-                               for bf16 inputs, 32; 0 = library default: 32 for
-                               bf16 inputs with M <= 128, else 64. Other values,
+                               for bf16 inputs, 32; 0 = the library's choice (bf16
+                               inputs: 64-token steps of the form that measured
+                               fastest; fp32: 64). Other values,
                                and 32 with fp32 inputs in a causal call, return
                                FAVOR_ERR_UNSUPPORTED. The result is the same sum
                                in another grouping                                 */
@@ -104,8 +105,8 @@ typedef struct {
                                sequence one workgroup scans chunk by chunk from
                                the aggregate of the segments before it (a multiple
                                of 64, at most 2^30); 0 = library default (about one
-                               workgroup per compute unit with T = 64, two with
-                               T = 32)                                             */
+                               workgroup per compute unit, two with T = 32 or,
+                               chunk = 0, with bf16 inputs and M <= 128)           */
 } favor_desc;
 
 /*

@@ -276,7 +276,8 @@ def attn_causal(Q, K, V, W, b, input_scale, denom_eps=0.0, state_in=None, return
                 chunk=0):
     """Unidirectional FAVOR by prefix sums (favor_attn_causal; favor_attn_causal_save
     when row_scale is given). segment: rows per causal segment (0 = library default);
-    chunk: tokens per step of the scan (0 = 64; bf16 inputs also take 32).
+    chunk: tokens per step of the scan (64; bf16 inputs also take 32; 0 = the library's
+    choice).
 
     Returns out, or (out, state_out [B, H, M, d+1]) when return_state is true.
     """

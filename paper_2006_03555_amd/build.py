@@ -20,7 +20,7 @@ LIB = os.path.join(HERE, "libfavor.so")
 ARCH = "gfx950"
 
 SOURCES = ["orf_draw.hip", "feature_map.hip", "bidir.hip", "causal.hip", "backward.hip",
-           "backward_scan.hip", "backward_f32.hip", "noalloc.hip", "probe.hip", "favor_api.cpp", "timing.cpp"]
+           "feature_scan.hip", "backward_f32.hip", "noalloc.hip", "probe.hip", "favor_api.cpp", "timing.cpp"]
 
 # Packed fp32 arithmetic is disabled for all device code (no v_pk_*_f32).
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -34,7 +34,7 @@ PER_SOURCE_FLAGS = {
     "bidir.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "causal.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", *_TRACKERS],
     "backward.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", *_TRACKERS],
-    "backward_scan.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", *_TRACKERS],
+    "feature_scan.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", *_TRACKERS],
     "backward_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", *_TRACKERS],
     # without it the probe's independent accumulators end up in rotating AGPR
     # ranges that chain every MFMA to the previous one

@@ -1181,7 +1181,7 @@ static hipError_t over_slices(const Shape &sh, bool accumulate, F &&f) {
   return hipSuccess;
 }
 
-// Causal scans of fp32 inputs (bf16: backward_scan.hip). accumulate: every slice
+// Causal scans of fp32 inputs (bf16: feature_scan.hip). accumulate: every slice
 // adds onto what dQ holds (the other direction's gradient, when both are
 // differentiated in one call).
 static hipError_t causal_dq_f32(const Shape &sh, const BwdArgs &a, hipStream_t st,

@@ -1303,6 +1303,8 @@ hipError_t launch_causal_save(const Shape &sh, Dt in, const void *Q, const void 
                               const float *prefix, void *o, float *rsave, int seg_len, int nseg,
                               float *halves, hipStream_t st) {
   if (!sh.renorm) return hipErrorInvalidValue;
+  if (in == Dt::BF16 && sh.feature_scan)
+    return launch_out_scan(sh, Dt::BF16, Q, K, V, wfr, bq, prefix, o, rsave, seg_len, nseg, st);
   if (in == Dt::BF16)
     return causal_fs_typed<bf16, true>(sh, Q, K, V, wfr, bq, prefix, o, seg_len, nseg, st, rsave);
   return causal_typed<float, float, true>(sh, Q, K, V, wfr, bq, prefix, o, seg_len, nseg, st,
@@ -1312,6 +1314,8 @@ hipError_t launch_causal_save(const Shape &sh, Dt in, const void *Q, const void 
 hipError_t launch_causal(const Shape &sh, Dt in, Dt out, const void *Q, const void *K,
                          const void *V, const void *wfr, const float *bq, const float *prefix,
                          void *o, int seg_len, int nseg, float *halves, hipStream_t st) {
+  if (in == Dt::BF16 && sh.feature_scan)
+    return launch_out_scan(sh, out, Q, K, V, wfr, bq, prefix, o, nullptr, seg_len, nseg, st);
   if (in == Dt::BF16)
     return out == Dt::BF16
                ? causal_fs_typed<bf16>(sh, Q, K, V, wfr, bq, prefix, o, seg_len, nseg, st)

@@ -82,9 +82,9 @@ constexpr int kMaxL = 1 << 30;
 constexpr int kChunk = 64;
 constexpr int kChunkSmall = 32;
 
-// The chunk length a call runs with: the descriptor's, or by default 32 for
-// bf16 inputs with at most 128 feature rows (two workgroups per CU scan those
-// faster) and 64 otherwise.
+// The chunk length a call's segments are planned for: the descriptor's, or by
+// default 32 for bf16 inputs with at most 128 feature rows (there two workgroups
+// of every causal scan share a CU) and 64 otherwise.
 int chunk_len(const favor_desc *g) {
   if (g->chunk != 0) return g->chunk;
   return g->in_dtype == FAVOR_BF16 && padded_m(g->M) <= 128 ? kChunkSmall : kChunk;
@@ -283,6 +283,7 @@ favor::Shape shape_of(const favor_desc *g) {
   sh.renorm = g->no_renormalize ? 0 : 1;
   sh.keps = g->kernel == FAVOR_KERNEL_RELU ? g->kernel_eps : 0.f;
   sh.chunk = chunk_len(g);
+  sh.feature_scan = g->chunk == 0;
   return sh;
 }
 

@@ -1,10 +1,10 @@
-// backward_scan.hip - the causal gradients of bf16 inputs: chunk scans with the
-// features split over the waves.
+// feature_scan.hip - the causal output and the causal gradients of bf16 inputs:
+// chunk scans with the features split over the waves.
 //
 // The notation is backward.hip's. One workgroup per (head, segment of the
-// forward plan) walks 64-token chunks, for dQ forwards with the aggregate
-// S = G^PS, for dK and dV backwards with R, the aggregate of the rows after
-// the chunk. Wave w owns M / NW features (NW = 8 waves; 4 at M = 64): its W''
+// forward plan) walks 64-token chunks, for the output and dQ forwards with the
+// aggregate S = G^PS, for dK and dV backwards with R, the aggregate of the rows
+// after the chunk. Wave w owns M / NW features (NW = 8 waves; 4 at M = 64): its W''
 // fragments, its slice of the aggregate (fp32 accumulators) and the chunk's
 // features of the other side never leave its registers, and every row fragment
 // it reads from LDS meets all of its features. What the waves exchange through
@@ -112,7 +112,7 @@ struct ScanSmem {
 // it is known otherwise. dQ of a renormalised row: g~ . q-hat = u . (Buf2 of the
 // row) = dout . buf3 - (dout . out) buf4, and out (buf4 + eps) = buf3, so it is
 // (dout . out) eps in units of q-hat: exactly 0 without a stabiliser. dK: it is
-// v . (R^T k-hat)[:d] + (R^T k-hat)[d], which k_bwd_dv_scan has at hand and saves
+// v . (R^T k-hat)[:d] + (R^T k-hat)[d], which k_out_scan has at hand and saves
 // (kdot). That leaves one sine, and no cosine, per x feature.
 // Wide: two barriers per chunk: P, (w U)^T and the next tile are formed while the
 // previous chunk's gradient is contracted; g~, the fold into the aggregate and
@@ -542,36 +542,40 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
   }
 }
 
-// ------------------------------------------------------------ causal dV
+// ------------------------------------------------------------ causal output and dV
 template <int M>
-struct DvSmem {
-  bf16 Z[tile_size<scan_wide(M)>()], X[tile_size<scan_wide(M)>()];   // the chunk's queries and keys (see tile_at)
+struct OutSmem {
+  bf16 Z[tile_size<scan_wide(M)>()], X[tile_size<scan_wide(M)>()];   // the chunk's rows (see tile_at)
   float D[2][64];               // D~ of the keys, by chunk parity
-  bf16x8 QA[4][M / 32][64];     // query features: lane = query, k = features
-  bf16x8 KF[4][M / 32][64];     // key features: lane = key, k = features
-  bf16x8 RB[4][M / 32][64];     // R^T before the chunk's rows: lane = value column, k = features
+  float E[2][64];               // forward: a query's stabiliser or factor (see below)
+  bf16x8 QA[4][M / 32][64];     // features of the z rows: lane = z, k = features
+  bf16x8 KF[4][M / 32][64];     // features of the x rows: lane = x, k = features
+  bf16x8 RB[4][M / 32][64];     // a^T without the chunk: lane = value column, k = features
   bf16x8 RE[M / 32][4];         // its last column, one fragment per lane group
-  bf16x8 UF[4][2][64];          // (alpha dout)^T: lane = value column, k = queries
-  bf16x8 UE[2][4];              // alpha u_d, one fragment per lane group
+  bf16x8 UF[4][2][64];          // (w u)^T: lane = value column, k = z rows
+  bf16x8 UE[2][4];              // u~'s last column, one fragment per lane group
   f32x4 red[scan_wide(M) ? 4 : 1][scan_wide(M) ? 5 : 1][64];   // the second half's partial sums
 };
 
-// dV_j = D~_j [R^T k-hat_j + sum over queries i >= j of the chunk of u~_i (q-hat_i . k-hat_j)],
-// chunks from the last to the first, and kdot_j = h_j . k-hat_j = v_j . (the bracket)
-// plus the bracket's last column, for dK. Each wave forms its features of the
-// queries and keys and publishes them and its slice of R (accumulators: rows =
-// features, lanes = value columns) in the layouts the products over all features
-// read; then wave (jb, half) takes key block jb: the masked q-hat . k-hat of one
-// 32-query half, its product with u~, and its share of R^T k-hat. The shares of
-// the feature steps even out the masked blocks (key block 0 meets eight query
-// blocks' worth, block 3 one).
-template <int M, int KN>
-__global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bwd_dv_scan(
-    const bf16 *__restrict__ Q, const bf16 *__restrict__ K, const bf16 *__restrict__ V,
-    const bf16 *__restrict__ dout, const float2 *__restrict__ aux,
-    const bf16x8 *__restrict__ wfr, const float *__restrict__ bqg,
-    const float *__restrict__ suffix, bf16 *__restrict__ dV, float *__restrict__ kdot, int H,
-    int L, int seg_len, int nseg, float s, float cM) {
+// The product of the x rows' features with the aggregate, plus the chunk's own part:
+//   B_x = a^T xf_x + sum over z rows of u~_z (zf_z . xf_x),  u~ = w [u, 1 or u_d],
+// with z <= x (FWD: x the queries, z and u the keys and values, chunks in order) or
+// z >= x (dV: x the keys, z and u the queries and output gradients, chunks from the
+// last).
+//   FWD: out_x = B_x[:d] / (B_x[d] + eps) (or the numerator times D_Q sqrt(2/M)), and
+//        SAVE: rowv_x, the row's 1 / (D-hat + eps) in units of the unscaled features
+//   dV:  dV_x = D~_x B_x[:d], and rowv_x = h . k-hat = v . B[:d] + B[d] for dK
+// Each wave forms its features of both row sets and publishes them and its slice
+// of the aggregate (accumulators: rows = features, lanes = value columns) in the
+// layouts the products over all features read; then wave (jb, half) takes x block
+// jb: the masked zf . xf of one 32-row half, its product with u~, and half of the
+// feature steps of a^T xf.
+template <typename To, int M, int KN, bool FWD, bool RN, bool SAVE>
+__global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_out_scan(
+    const bf16 *__restrict__ X, const bf16 *__restrict__ Z, const bf16 *__restrict__ U,
+    const bf16 *__restrict__ V, const float2 *__restrict__ aux, const bf16x8 *__restrict__ wfr,
+    const float *__restrict__ bqg, const float *__restrict__ states, To *__restrict__ out,
+    float *__restrict__ rowv, int H, int L, int seg_len, int nseg, float s, float eps, float cM) {
   constexpr int NW = scan_waves(M);
   constexpr int FB = M / 16 / NW;
   constexpr int NS = M / 32;
@@ -579,7 +583,7 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
   constexpr bool kWide = scan_wide(M);
   using P = Mma<bf16>;
   using frag = bf16x8;
-  __shared__ DvSmem<M> sm;
+  __shared__ OutSmem<M> sm;
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int bh = item / nseg;
   const int seg = item - bh * nseg;
@@ -595,18 +599,18 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
   const int r1 = min(L, r0 + seg_len);
   if (r0 >= r1) return;
   const int nch = (r1 - r0 + 63) / 64;
-  const bf16 *Qh = Q + (size_t)bh * L * kD;
-  const bf16 *Kh = K + (size_t)bh * L * kD;
-  const bf16 *Vh = V + (size_t)bh * L * kD;
-  const bf16 *dOh = dout + (size_t)bh * L * kD;
-  const float2 *auh = aux + (size_t)bh * L;
+  const bf16 *Xh = X + (size_t)bh * L * kD;
+  const bf16 *Zh = Z + (size_t)bh * L * kD;
+  const bf16 *Uh = U + (size_t)bh * L * kD;
+  const bf16 *Vh = FWD ? nullptr : V + (size_t)bh * L * kD;
+  const float2 *auh = FWD ? nullptr : aux + (size_t)bh * L;
   const int jb = w & 3;
 
   // the next chunk's rows: queries and keys to be staged, and the output
   // gradients this wave transposes (row block w % 4, columns 32 (w / 4 + k) ..)
   struct Regs {
     frag z[RPT], x[RPT], u[RPT];
-    float2 a[4];   // row weights of queries 16 (w % 4) + 4 g + j
+    float2 a[FWD ? 1 : 4];   // dV: row weights of queries 16 (w % 4) + 4 g + j
   };
   Regs rg;
   auto load_rows = [&](int t0) __attribute__((always_inline)) {
@@ -616,16 +620,18 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
       const size_t off = (size_t)t * kD + 8 * (tid & 7);
       rg.z[k] = rg.x[k] = rg.u[k] = P::splat(0.f);
       if (t < r1) {
-        rg.z[k] = load_frag<bf16>(Qh + off);
-        rg.x[k] = load_frag<bf16>(Kh + off);
+        rg.z[k] = load_frag<bf16>(Zh + off);
+        rg.x[k] = load_frag<bf16>(Xh + off);
       }
       const int tu = t0 + 16 * (w & 3) + c16;
-      if (tu < r1) rg.u[k] = load_frag<bf16>(dOh + (size_t)tu * kD + 32 * ((w >> 2) + k) + 8 * g);
+      if (tu < r1) rg.u[k] = load_frag<bf16>(Uh + (size_t)tu * kD + 32 * ((w >> 2) + k) + 8 * g);
     }
+    if constexpr (!FWD) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int t = t0 + 16 * (w & 3) + 4 * g + j;
-      rg.a[j] = t < r1 ? auh[t] : make_float2(0.f, 0.f);
+      for (int j = 0; j < 4; ++j) {
+        const int t = t0 + 16 * (w & 3) + 4 * g + j;
+        rg.a[j] = t < r1 ? auh[t] : make_float2(0.f, 0.f);
+      }
     }
   };
   auto stage_rows = [&](int t0, int par) __attribute__((always_inline)) {
@@ -634,12 +640,18 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
       const int r = (tid >> 3) + 8 * NW * k;
       store_frag<bf16>(&sm.Z[tile_at<kWide>(r, tid & 7)], rg.z[k]);
       store_frag<bf16>(&sm.X[tile_at<kWide>(r, tid & 7)], rg.x[k]);
+      const frag &kr = FWD ? rg.z[k] : rg.x[k];
       float D = 1.f;
-      if constexpr (KN == kCos) D = cM * expf(s2half * oct_sum_f32(dot8(rg.x[k], rg.x[k])));
-      if ((tid & 7) == 0) sm.D[par][r] = D;
+      if constexpr (KN == kCos) D = cM * expf(s2half * oct_sum_f32(dot8(kr, kr)));
+      if ((tid & 7) == 0) sm.D[par][r] = !FWD || t0 + r < r1 ? D : 0.f;
+      if (FWD && KN == kCos && (!RN || eps != 0.f)) {
+        // D_Q sqrt(2/M), which the features omit, or the stabiliser divided by it
+        const float dq = cM * expf(s2half * oct_sum_f32(dot8(rg.x[k], rg.x[k])));
+        if ((tid & 7) == 0) sm.E[par][r] = RN ? eps / dq : dq;
+      }
     }
   };
-  auto chunk_t0 = [&](int c) { return r0 + 64 * (nch - 1 - c); };
+  auto chunk_t0 = [&](int c) { return r0 + 64 * (FWD ? c : nch - 1 - c); };
   load_rows(chunk_t0(0));
 
   frag wf[FB][2];
@@ -659,7 +671,7 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
   // (block 4: the last column, replicated)
   f32x4 acc[FB][5];
   {
-    const float *R = suffix + ((size_t)bh * nseg + seg) * M * 65;
+    const float *R = states + ((size_t)bh * nseg + seg) * M * 65;
 #pragma unroll
     for (int mb = 0; mb < FB; ++mb)
 #pragma unroll
@@ -683,6 +695,19 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
 #pragma unroll
       for (int nb = 0; nb < 5; ++nb) va[nb] += sm.red[jb][nb][l];
     }
+    if constexpr (FWD) {
+      float e = RN ? (KN == kCos ? 0.f : eps) : 1.f;
+      if (KN == kCos && (!RN || eps != 0.f)) e = sm.E[c & 1][16 * jb + c16];
+      const float inv = RN ? 1.0f / (va[4][0] + e) : e;
+      if (j < r1) {
+#pragma unroll
+        for (int pp = 0; pp < 2; ++pp)
+          store8(out + ((size_t)bh * L + j) * kD + 32 * pp + 8 * g, va[2 * pp] * inv,
+                 va[2 * pp + 1] * inv);
+        if (SAVE && g == 0) rowv[(size_t)bh * L + j] = inv;
+      }
+      return;
+    }
     const float D = sm.D[c & 1][16 * jb + c16];
     if constexpr (KN == kCos) {
       float d = 0.f;
@@ -695,12 +720,12 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
         }
       d += __shfl_xor(d, 16);
       d += __shfl_xor(d, 32);
-      if (g == 0 && j < r1) kdot[(size_t)bh * L + j] = d + va[4][0];
+      if (g == 0 && j < r1) rowv[(size_t)bh * L + j] = d + va[4][0];
     }
     if (j < r1) {
 #pragma unroll
       for (int pp = 0; pp < 2; ++pp)
-        store8(dV + ((size_t)bh * L + j) * kD + 32 * pp + 8 * g, va[2 * pp] * D,
+        store8(out + ((size_t)bh * L + j) * kD + 32 * pp + 8 * g, va[2 * pp] * D,
                va[2 * pp + 1] * D);
     }
   };
@@ -712,15 +737,20 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
     for (int k = 0; k < RPT; ++k) {
       const int tb = w & 3;
       const int kh = (w >> 2) + k;
-      const f32x4 wz = {rg.a[0].x, rg.a[1].x, rg.a[2].x, rg.a[3].x};
+      f32x4 wz, ez;
+      if constexpr (FWD) {
+        wz = ez = *reinterpret_cast<const f32x4 *>(&sm.D[c & 1][16 * tb + 4 * g]);
+      } else {
+        wz = f32x4{rg.a[0].x, rg.a[1].x, rg.a[2].x, rg.a[3].x};
+        ez = f32x4{rg.a[0].y, rg.a[1].y, rg.a[2].y, rg.a[3].y};
+      }
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
         const f32x4 t = P::mma(rg.u[k], scan_select(half), zero4);
         store_half_frag(&sm.UF[2 * kh + half][tb >> 1][l], tb & 1, t * wz);
       }
       if (kh == 0 && c16 == 0)
-        store_half_frag(&sm.UE[tb >> 1][g], tb & 1,
-                        f32x4{rg.a[0].y, rg.a[1].y, rg.a[2].y, rg.a[3].y});
+        store_half_frag(&sm.UE[tb >> 1][g], tb & 1, ez);
     }
     // R^T before the chunk's rows
 #pragma unroll
@@ -791,7 +821,7 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
     __syncthreads();
 
     if (c + 1 < nch) load_rows(chunk_t0(c + 1));
-    {
+    if constexpr (!FWD) {
       const int j = t0 + 16 * jb + c16;
       vr[0] = vr[1] = P::splat(0.f);
       if (KN == kCos && j < r1) {
@@ -817,7 +847,7 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
       const int zs = (w >> 2) + k;
-      if (2 * zs + 1 < jb) continue;   // queries before the keys
+      if (FWD ? 2 * zs > jb : 2 * zs + 1 < jb) continue;   // wholly masked
       f32x4 p4[2] = {zero4, zero4};
 #pragma unroll
       for (int ks = 0; ks < NS; ++ks)
@@ -827,7 +857,10 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
       for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          p4[q][e] = 16 * (2 * zs + q) + 4 * g + e >= 16 * jb + c16 ? p4[q][e] : 0.f;
+        {
+          const int z = 16 * (2 * zs + q) + 4 * g + e, x = 16 * jb + c16;
+          p4[q][e] = (FWD ? z <= x : z >= x) ? p4[q][e] : 0.f;
+        }
       const frag pb = P::pack(p4[0], p4[1]);
 #pragma unroll
       for (int nb = 0; nb < 5; ++nb)
@@ -895,11 +928,12 @@ hipError_t launch_bwd_dq_scan(const Shape &sh, const BwdArgs &a, bool accumulate
 template <int KN>
 static hipError_t dv_scan(const Shape &sh, const BwdArgs &a, hipStream_t st) {
   FAVOR_SCAN_DISPATCH_M(
-      sh.M, hipLaunchKernelGGL((k_bwd_dv_scan<MM, KN>), dim3(a.nseg * sh.BH),
-                               dim3(64 * scan_waves(MM)), 0, st, (const bf16 *)a.Q,
-                               (const bf16 *)a.K, (const bf16 *)a.V, (const bf16 *)a.dout, a.aux,
-                               (const bf16x8 *)a.wfr, a.bq, a.state, (bf16 *)a.dV, a.kdot, sh.H,
-                               sh.L, a.seg_len, a.nseg, sh.s, feature_norm(sh)));
+      sh.M, hipLaunchKernelGGL((k_out_scan<bf16, MM, KN, false, true, false>),
+                               dim3(a.nseg * sh.BH), dim3(64 * scan_waves(MM)), 0, st,
+                               (const bf16 *)a.K, (const bf16 *)a.Q, (const bf16 *)a.dout,
+                               (const bf16 *)a.V, a.aux, (const bf16x8 *)a.wfr, a.bq, a.state,
+                               (bf16 *)a.dV, a.kdot, sh.H, sh.L, a.seg_len, a.nseg, sh.s, 0.f,
+                               feature_norm(sh)));
   return hipGetLastError();
 }
 
@@ -909,6 +943,46 @@ hipError_t launch_bwd_dkv_scan(const Shape &sh, const BwdArgs &a, hipStream_t st
   if (e != hipSuccess) return e;
   return sh.kernel == 1 ? row_scan<kRelu, true, true, false>(sh, a, st)
                         : row_scan<kCos, true, true, false>(sh, a, st);
+}
+
+// The forward scan from the segments' prefix states.
+template <typename To, int KN, bool RN, bool SAVE>
+static hipError_t fwd_scan(const Shape &sh, const void *Q, const void *K, const void *V,
+                           const void *wfr, const float *bq, const float *prefix, void *o,
+                           float *rsave, int seg_len, int nseg, hipStream_t st) {
+  FAVOR_SCAN_DISPATCH_M(
+      sh.M, hipLaunchKernelGGL((k_out_scan<To, MM, KN, true, RN, SAVE>), dim3(nseg * sh.BH),
+                               dim3(64 * scan_waves(MM)), 0, st, (const bf16 *)Q,
+                               (const bf16 *)K, (const bf16 *)V, (const bf16 *)nullptr,
+                               (const float2 *)nullptr, (const bf16x8 *)wfr, bq, prefix, (To *)o,
+                               rsave, sh.H, sh.L, seg_len, nseg, sh.s, sh.eps, feature_norm(sh)));
+  return hipGetLastError();
+}
+
+template <typename To, bool SAVE>
+static hipError_t fwd_scan_kind(const Shape &sh, const void *Q, const void *K, const void *V,
+                                const void *wfr, const float *bq, const float *prefix, void *o,
+                                float *rsave, int seg_len, int nseg, hipStream_t st) {
+  if (!sh.renorm) {
+    if constexpr (SAVE) return hipErrorInvalidValue;
+    else
+      return sh.kernel == 1
+                 ? fwd_scan<To, kRelu, false, false>(sh, Q, K, V, wfr, bq, prefix, o, rsave, seg_len, nseg, st)
+                 : fwd_scan<To, kCos, false, false>(sh, Q, K, V, wfr, bq, prefix, o, rsave, seg_len, nseg, st);
+  }
+  return sh.kernel == 1
+             ? fwd_scan<To, kRelu, true, SAVE>(sh, Q, K, V, wfr, bq, prefix, o, rsave, seg_len, nseg, st)
+             : fwd_scan<To, kCos, true, SAVE>(sh, Q, K, V, wfr, bq, prefix, o, rsave, seg_len, nseg, st);
+}
+
+hipError_t launch_out_scan(const Shape &sh, Dt out, const void *Q, const void *K, const void *V,
+                           const void *wfr, const float *bq, const float *prefix, void *o,
+                           float *rsave, int seg_len, int nseg, hipStream_t st) {
+  if (rsave)
+    return fwd_scan_kind<bf16, true>(sh, Q, K, V, wfr, bq, prefix, o, rsave, seg_len, nseg, st);
+  return out == Dt::BF16
+             ? fwd_scan_kind<bf16, false>(sh, Q, K, V, wfr, bq, prefix, o, rsave, seg_len, nseg, st)
+             : fwd_scan_kind<float, false>(sh, Q, K, V, wfr, bq, prefix, o, rsave, seg_len, nseg, st);
 }
 
 }  // namespace favor

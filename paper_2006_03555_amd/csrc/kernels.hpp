@@ -29,6 +29,13 @@ struct Shape {
   int renorm;    // 1 divide by D-hat, 0 return the numerator Q' K'^T V
   float keps;    // ReLU: added to every feature
   int chunk;     // tokens per step of the causal scan: 64, or 32 (bf16 inputs)
+  // causal scan of bf16 inputs: k_out_scan (64-token chunks, products over all
+  // features through LDS) where the caller leaves the chunk length to the library,
+  // k_causal_fs with `chunk` where it names one. Per launch (us): B4 H8 L8192 M256
+  // 71.7 against 82.1 (T = 64), B1 H16 L65536 M256 289 against 311, B8 H8 L2047
+  // M128 25.4 against 27.6 (T = 32). Whole calls: both directions of B4 H8 L8192
+  // 161 -> 151, B1 H16 L65536 389 -> 354.
+  int feature_scan;
 };
 
 // Scales of the projection W'' = ws W and of its seed b'' = bs b for the
@@ -123,9 +130,13 @@ struct BwdArgs {
 hipError_t launch_bwd_dq(const Shape &sh, Dt in, bool causal, const BwdArgs &a, hipStream_t st,
                          bool accumulate = false);
 hipError_t launch_bwd_dkv(const Shape &sh, Dt in, bool causal, const BwdArgs &a, hipStream_t st);
-// The causal gradients of bf16 inputs (backward_scan.hip).
+// The causal gradients of bf16 inputs (feature_scan.hip).
 hipError_t launch_bwd_dq_scan(const Shape &sh, const BwdArgs &a, bool accumulate, hipStream_t st);
 hipError_t launch_bwd_dkv_scan(const Shape &sh, const BwdArgs &a, hipStream_t st);
+// The causal forward scan in the same form (bf16 inputs; rsave nullable).
+hipError_t launch_out_scan(const Shape &sh, Dt out, const void *Q, const void *K, const void *V,
+                           const void *wfr, const float *bq, const float *prefix, void *o,
+                           float *rsave, int seg_len, int nseg, hipStream_t st);
 // The bidirectional gradients of fp32 inputs (backward_f32.hip).
 hipError_t launch_bwd_dq_f32(const Shape &sh, const BwdArgs &a, hipStream_t st);
 hipError_t launch_bwd_dkv_f32(const Shape &sh, const BwdArgs &a, hipStream_t st);

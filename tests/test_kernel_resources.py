@@ -85,10 +85,10 @@ def test_causal_gradient_scans_fit(tmp_path_factory):
     """The bf16 causal gradient scans hold their registers without scratch; at
     M <= 128 two workgroups share a CU (half its LDS, at most 256 registers per
     wave of their four), at M = 256 one of eight waves fills it."""
-    kernels = _kernel_descriptors(tmp_path_factory, "backward_scan.hip")
+    kernels = _kernel_descriptors(tmp_path_factory, "feature_scan.hip")
     assert kernels
     for name, f in kernels.items():
         assert f["private_segment_fixed_size"] == 0, name
         assert f["next_free_vgpr"] <= REGS_PER_LANE // 2, (name, f["next_free_vgpr"])
-        wide = "ILi256E" in name
+        wide = "Li256E" in name
         assert f["group_segment_fixed_size"] <= LDS_PER_CU // (1 if wide else 2), name
