@@ -756,7 +756,7 @@ favor_status favor_attn_bidir_backward(const favor_desc *g, const void *Q, const
     if (e != hipSuccess) return device_result(e, "favor_attn_bidir_backward Buf1");
   }
   favor::BwdArgs a{Q,  K,  V,  dout, saved ? out_fwd : w.out, saved ? row_scale : w.rsave,
-                   wfr, bq, W, buf1, dQ, dK, dV, w.aux, p.rows_per_split, p.nsplit, nullptr};
+                   wfr, bq, W, buf1, dQ, dK, dV, w.aux, p.rows_per_split, p.nsplit};
   {
     favor::LaunchTimer t(favor::kKerBwdDq, st);
     e = favor::launch_bwd_dq(sh, in, false, a, st);
@@ -852,8 +852,7 @@ favor_status favor_attn_causal_backward(const favor_desc *g, const void *Q, cons
     if (e != hipSuccess) return device_result(e, "favor_attn_causal_backward forward pass");
   }
   favor::BwdArgs a{Q,  K,  V,  dout, saved ? out_fwd : w.out, saved ? row_scale : w.rsave,
-                   wfr, bq, W, prefix, dQ, dK, dV, w.aux, p.rows_per_split, p.nsplit,
-                   /*kdot: the query gradients read rsave for the last time*/ w.rsave};
+                   wfr, bq, W, prefix, dQ, dK, dV, w.aux, p.rows_per_split, p.nsplit};
   {
     favor::LaunchTimer t(favor::kKerBwdDq, st);
     e = favor::launch_bwd_dq(sh, in, true, a, st);
@@ -961,7 +960,7 @@ favor_status favor_attn_both_backward(const favor_desc *g, const void *Q, const 
   // bidirectional: dQ of its rows, then dBuf1 = sum of q-hat (x) u~ over every row
   favor::BwdArgs ab{Q,   K,   V,   dout_bidir, saved_b ? out_bidir : wb.out,
                     saved_b ? row_scale_bidir : wb.rsave, wfr, bq, W, buf1, dQ, dK, dV,
-                    wb.aux, pb.rows_per_split, pb.nsplit, nullptr};
+                    wb.aux, pb.rows_per_split, pb.nsplit};
   {
     favor::LaunchTimer t(favor::kKerBwdDq, st);
     e = favor::launch_bwd_dq(sh, in, false, ab, st);
@@ -983,7 +982,7 @@ favor_status favor_attn_both_backward(const favor_desc *g, const void *Q, const 
   // one key pass gives dK and dV of both directions
   favor::BwdArgs ac{Q,   K,   V,   dout_causal, saved_c ? out_causal : wc.out,
                     saved_c ? row_scale_causal : wc.rsave, wfr, bq, W, prefix, dQ, dK, dV,
-                    wc.aux, pc.rows_per_split, pc.nsplit, wc.rsave};
+                    wc.aux, pc.rows_per_split, pc.nsplit};
   {
     favor::LaunchTimer t(favor::kKerBwdDq, st);
     e = favor::launch_bwd_dq(sh, in, true, ac, st, /*accumulate=*/true);

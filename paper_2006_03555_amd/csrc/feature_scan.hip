@@ -92,11 +92,10 @@ struct ScanSmem {
   bf16x8 UF[4][2][64];          // (w U)^T: row = value column (permuted), k = z rows
   bf16x8 PF[4][2][64];          // P of x block, z half: B operand, k = 32 z rows
   bf16x8 GF[4][M / 32][64];     // gradient of the projections: lane = x row, k = features
-  float dots[scan_waves(M)][64];   // without renormalisation: g~ . features, per wave
+  float dots[scan_waves(M)][64];   // g~ . xf of each wave's features (cos)
   bf16x8 WT[scan_wide(M) ? 4 : 1][M / 32][64];   // W^T: lane = input column (permuted), k = features
   float sz[M];                  // last column of the aggregate before the chunk
   float ox[2][64];              // factor of an x row's gradient, by chunk parity: alpha (dQ) or D~ (dK)
-  float cx[2][64];              // factor of x itself in it: s^2 g~ . xf (see k_bwd_row_scan)
   // else, to save registers: the selection fragments and b''
   bf16x8 sel[scan_wide(M) ? 1 : 2][64];
   float bq[scan_wide(M) ? 4 : M];
@@ -108,12 +107,12 @@ struct ScanSmem {
 //   g~[m][x] = a y + zf^T P + a_d uy       (one accumulation)
 //   grad x = ox (W^T (g~ o slope) + s^2 (g~ . xf) x)      (cos features)
 //   a += zf (x) [w u, e]
-// The dot product g~ . xf of cos features is not summed over the features where
-// it is known otherwise. dQ of a renormalised row: g~ . q-hat = u . (Buf2 of the
-// row) = dout . buf3 - (dout . out) buf4, and out (buf4 + eps) = buf3, so it is
-// (dout . out) eps in units of q-hat: exactly 0 without a stabiliser. dK: it is
-// v . (R^T k-hat)[:d] + (R^T k-hat)[d], which k_out_scan has at hand and saves
-// (kdot). That leaves one sine, and no cosine, per x feature.
+// The dot product g~ . xf of cos features is summed over the features of the very
+// g~ and xf that the first term takes: their bf16 errors then cancel in part. The
+// closed forms (u . Buf2 of a renormalised row: exactly 0 without a stabiliser; dK:
+// v . (R^T k-hat)[:d] + (R^T k-hat)[d] from the dV pass) save the cosines but are
+// further from 64 bits: B2 H8 L2048 M256 dQ 4.9e-3 against 4.5e-3, dK 4.6e-3 against
+// 4.3e-3 (relative 2-norms).
 // Wide: two barriers per chunk: P, (w U)^T and the next tile are formed while the
 // previous chunk's gradient is contracted; g~, the fold into the aggregate and
 // the staging of the next tile follow the first barrier, the contraction with W
@@ -125,9 +124,8 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
     const bf16 *__restrict__ dout, const bf16 *__restrict__ out, const float *__restrict__ rsave,
     const bf16x8 *__restrict__ wfr, const float *__restrict__ bqg, const float *__restrict__ W,
     const float *__restrict__ states, bf16 *__restrict__ dX, float2 *__restrict__ aux,
-    const float *__restrict__ kdot, int H, int L, int seg_len, int nseg, float s, float eps,
-    int Mr, float cM, float wts) {
-  constexpr bool kDot = KN == kCos && !KEY && !RN;   // sum g~ . xf over the features
+    int H, int L, int seg_len, int nseg, float s, int Mr, float cM, float wts) {
+  constexpr bool kDot = KN == kCos;
   constexpr int NW = scan_waves(M);
   constexpr int FB = M / 16 / NW;      // 16-feature blocks per wave
   constexpr int NS = M / 32;           // feature steps of the last contraction
@@ -184,7 +182,6 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
         rg[k].u = load_frag<bf16>(Uh + off);
         if constexpr (KEY) {
           rg[k].a = auh[t];
-          if constexpr (KN == kCos) rg[k].rs = kdot[(size_t)bh * L + t];
         } else if constexpr (RN) {
           rg[k].o = load_frag<bf16>(Oh + off);
           rg[k].rs = rsh[t];
@@ -209,9 +206,8 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
         D = cM * expf(s2half * oct_sum_f32(dot8(kr, kr)));
       }
       D = t < r1 ? D : 0.f;
-      float wz, ez, uy, ox, cx = 0.f;
+      float wz, ez, uy, ox;
       if constexpr (KEY) {
-        if constexpr (KN == kCos) cx = s * s * rg[k].rs;
         wz = rg[k].a.x;
         ez = rg[k].a.y;
         uy = 1.f;
@@ -222,10 +218,6 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
         if constexpr (RN) {
           ox = rg[k].rs;
           uy = -oct_sum_f32(dot8(rg[k].y, rg[k].o));
-          if (KN == kCos && eps != 0.f) {   // eps in units of q-hat: eps / (D_Q sqrt(2/M))
-            const float dq = cM * expf(s2half * oct_sum_f32(dot8(rg[k].x, rg[k].x)));
-            cx = t < r1 ? -s * s * uy * (eps / dq) : 0.f;
-          }
         } else {
           float a = 1.f;
           if constexpr (KN == kCos) a = cM * expf(s2half * oct_sum_f32(dot8(rg[k].x, rg[k].x)));
@@ -239,7 +231,6 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
         tl.ez[r] = ez;
         tl.uy[r] = uy;
         sm.ox[par][r] = ox;
-        sm.cx[par][r] = cx;
         reinterpret_cast<bf16 *>(&tl.EF[r >> 5][(r >> 2) & 3])[4 * ((r >> 4) & 1) + (r & 3)] =
             (bf16)ez;
       }
@@ -506,7 +497,7 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_bw
     for (int q = 0; q < NT; ++q) {
       const int x = 16 * (kWide ? w & 3 : q) + c16;
       const float ox = sm.ox[c & 1][x];
-      float cx = sm.cx[c & 1][x];
+      float cx = 0.f;   // factor of the row itself: s^2 g~ . xf
       if constexpr (kDot) {
         float d = 0.f;
 #pragma unroll
@@ -564,7 +555,7 @@ struct OutSmem {
 // last).
 //   FWD: out_x = B_x[:d] / (B_x[d] + eps) (or the numerator times D_Q sqrt(2/M)), and
 //        SAVE: rowv_x, the row's 1 / (D-hat + eps) in units of the unscaled features
-//   dV:  dV_x = D~_x B_x[:d], and rowv_x = h . k-hat = v . B[:d] + B[d] for dK
+//   dV:  dV_x = D~_x B_x[:d]
 // Each wave forms its features of both row sets and publishes them and its slice
 // of the aggregate (accumulators: rows = features, lanes = value columns) in the
 // layouts the products over all features read; then wave (jb, half) takes x block
@@ -573,7 +564,7 @@ struct OutSmem {
 template <typename To, int M, int KN, bool FWD, bool RN, bool SAVE>
 __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_out_scan(
     const bf16 *__restrict__ X, const bf16 *__restrict__ Z, const bf16 *__restrict__ U,
-    const bf16 *__restrict__ V, const float2 *__restrict__ aux, const bf16x8 *__restrict__ wfr,
+    const float2 *__restrict__ aux, const bf16x8 *__restrict__ wfr,
     const float *__restrict__ bqg, const float *__restrict__ states, To *__restrict__ out,
     float *__restrict__ rowv, int H, int L, int seg_len, int nseg, float s, float eps, float cM) {
   constexpr int NW = scan_waves(M);
@@ -602,7 +593,6 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
   const bf16 *Xh = X + (size_t)bh * L * kD;
   const bf16 *Zh = Z + (size_t)bh * L * kD;
   const bf16 *Uh = U + (size_t)bh * L * kD;
-  const bf16 *Vh = FWD ? nullptr : V + (size_t)bh * L * kD;
   const float2 *auh = FWD ? nullptr : aux + (size_t)bh * L;
   const int jb = w & 3;
 
@@ -686,7 +676,6 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
   __syncthreads();
 
   f32x4 va[5];     // this wave's share of the bracket: value blocks, last column
-  frag vr[2];      // the value rows of its keys
   // after the barrier that publishes the second half's shares: sum, store
   auto finish = [&](int c) __attribute__((always_inline)) {
     if (kWide && w >= 4) return;
@@ -709,19 +698,6 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
       return;
     }
     const float D = sm.D[c & 1][16 * jb + c16];
-    if constexpr (KN == kCos) {
-      float d = 0.f;
-#pragma unroll
-      for (int pp = 0; pp < 2; ++pp)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          d = fmaf((float)vr[pp][e], va[2 * pp][e], d);
-          d = fmaf((float)vr[pp][4 + e], va[2 * pp + 1][e], d);
-        }
-      d += __shfl_xor(d, 16);
-      d += __shfl_xor(d, 32);
-      if (g == 0 && j < r1) rowv[(size_t)bh * L + j] = d + va[4][0];
-    }
     if (j < r1) {
 #pragma unroll
       for (int pp = 0; pp < 2; ++pp)
@@ -821,14 +797,6 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
     __syncthreads();
 
     if (c + 1 < nch) load_rows(chunk_t0(c + 1));
-    if constexpr (!FWD) {
-      const int j = t0 + 16 * jb + c16;
-      vr[0] = vr[1] = P::splat(0.f);
-      if (KN == kCos && j < r1) {
-        vr[0] = load_frag<bf16>(Vh + (size_t)j * kD + 8 * g);
-        vr[1] = load_frag<bf16>(Vh + (size_t)j * kD + 32 + 8 * g);
-      }
-    }
     // fold the chunk's rows into R
 #pragma unroll
     for (int zs = 0; zs < 2; ++zs)
@@ -862,9 +830,24 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
           p4[q][e] = (FWD ? z <= x : z >= x) ? p4[q][e] : 0.f;
         }
       const frag pb = P::pack(p4[0], p4[1]);
+      // The intra-chunk weights as two bf16 terms. One rounding of the whole sum over
+      // the features is a larger error than k_causal_fs's roundings of its four partial
+      // sums, and dV reads the row scales that the output's weights gave: B2 H8 L2048
+      // M256, relative 2-norms, output 2.5e-3 against 2.7e-3 with one term
+      // (k_causal_fs: 2.6e-3). The extra products take 1.7 us of 66 in the output scan
+      // of B4 H8 L8192 M256.
+      f32x4 lo[2];
 #pragma unroll
-      for (int nb = 0; nb < 5; ++nb)
-        va[nb] = P::mma(nb < 4 ? sm.UF[nb][zs][l] : sm.UE[zs][g], pb, va[nb]);
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) lo[q][e] = p4[q][e] - (float)pb[4 * q + e];
+      const frag pl = P::pack(lo[0], lo[1]);
+#pragma unroll
+      for (int nb = 0; nb < 5; ++nb) {
+        const frag u = nb < 4 ? sm.UF[nb][zs][l] : sm.UE[zs][g];
+        va[nb] = P::mma(u, pb, va[nb]);
+        va[nb] = P::mma(u, pl, va[nb]);
+      }
     }
     // R^T k-hat (wide: this half's feature steps)
     constexpr int kSteps = kWide ? NS / 2 : NS;
@@ -905,8 +888,8 @@ static hipError_t row_scan(const Shape &sh, const BwdArgs &a, hipStream_t st) {
                                dim3(64 * scan_waves(MM)), 0, st, (const bf16 *)a.Q,
                                (const bf16 *)a.K, (const bf16 *)a.V, (const bf16 *)a.dout,
                                (const bf16 *)a.out, a.rsave, (const bf16x8 *)a.wfr, a.bq, a.W,
-                               a.state, (bf16 *)(KEY ? a.dK : a.dQ), a.aux, a.kdot, sh.H, sh.L,
-                               a.seg_len, a.nseg, sh.s, sh.eps, sh.Mr, feature_norm(sh), wts));
+                               a.state, (bf16 *)(KEY ? a.dK : a.dQ), a.aux, sh.H, sh.L, a.seg_len,
+                               a.nseg, sh.s, sh.Mr, feature_norm(sh), wts));
   return hipGetLastError();
 }
 
@@ -931,13 +914,12 @@ static hipError_t dv_scan(const Shape &sh, const BwdArgs &a, hipStream_t st) {
       sh.M, hipLaunchKernelGGL((k_out_scan<bf16, MM, KN, false, true, false>),
                                dim3(a.nseg * sh.BH), dim3(64 * scan_waves(MM)), 0, st,
                                (const bf16 *)a.K, (const bf16 *)a.Q, (const bf16 *)a.dout,
-                               (const bf16 *)a.V, a.aux, (const bf16x8 *)a.wfr, a.bq, a.state,
-                               (bf16 *)a.dV, a.kdot, sh.H, sh.L, a.seg_len, a.nseg, sh.s, 0.f,
+                               a.aux, (const bf16x8 *)a.wfr, a.bq, a.state,
+                               (bf16 *)a.dV, (float *)nullptr, sh.H, sh.L, a.seg_len, a.nseg, sh.s, 0.f,
                                feature_norm(sh)));
   return hipGetLastError();
 }
 
-// dV first: it leaves kdot for dK.
 hipError_t launch_bwd_dkv_scan(const Shape &sh, const BwdArgs &a, hipStream_t st) {
   const hipError_t e = sh.kernel == 1 ? dv_scan<kRelu>(sh, a, st) : dv_scan<kCos>(sh, a, st);
   if (e != hipSuccess) return e;
@@ -953,7 +935,7 @@ static hipError_t fwd_scan(const Shape &sh, const void *Q, const void *K, const 
   FAVOR_SCAN_DISPATCH_M(
       sh.M, hipLaunchKernelGGL((k_out_scan<To, MM, KN, true, RN, SAVE>), dim3(nseg * sh.BH),
                                dim3(64 * scan_waves(MM)), 0, st, (const bf16 *)Q,
-                               (const bf16 *)K, (const bf16 *)V, (const bf16 *)nullptr,
+                               (const bf16 *)K, (const bf16 *)V,
                                (const float2 *)nullptr, (const bf16x8 *)wfr, bq, prefix, (To *)o,
                                rsave, sh.H, sh.L, seg_len, nseg, sh.s, sh.eps, feature_norm(sh)));
   return hipGetLastError();

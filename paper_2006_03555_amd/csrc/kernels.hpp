@@ -124,7 +124,6 @@ struct BwdArgs {
   void *dQ, *dK, *dV;
   float2 *aux;           // [BH][L] (alpha, alpha u_d)
   int seg_len, nseg;     // causal: the segments of the forward plan
-  float *kdot;           // causal bf16: [BH][L] scratch from dV to dK (h . k-hat per key)
 };
 // accumulate (causal only): add onto dQ instead of overwriting it.
 hipError_t launch_bwd_dq(const Shape &sh, Dt in, bool causal, const BwdArgs &a, hipStream_t st,

@@ -1,7 +1,7 @@
 """The bf16 causal gradient scans (features split over the waves) at the sizes
 where they can go wrong: one row, chunk and segment edges, every padded feature
 count, both feature kinds, the paths with and without renormalisation and
-stabiliser (the dot product g~ . q-hat is summed, zero or eps-scaled), a carried
+stabiliser (g~ . q-hat is zero up to the stabiliser where renormalised), a carried
 state with a state gradient, saved and recomputed statistics. Gate as in
 test_gpu_backward."""
 import numpy as np

@@ -1,0 +1,40 @@
+"""The default causal scan of bf16 inputs is no further from 64 bits than the
+64-token chunk scan it stands in for (chunk=64), which rounds the intra-chunk
+weights as four partial sums."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from helpers import to_dev, to_host
+from oracle import favor
+
+pytestmark = pytest.mark.gpu
+
+S64 = 64 ** -0.25
+
+
+# a few and many segments, ragged; every width the scan is built for
+@pytest.mark.parametrize("L", [200, 700])
+@pytest.mark.parametrize("M", [112, 128, 208, 256])
+@pytest.mark.parametrize("kernel", ["softmax", "relu"])
+def test_default_scan_no_less_precise(L, M, kernel):
+    fv = __import__("paper_2006_03555_amd")
+    kn = favor.KERNEL_RELU if kernel == "relu" else favor.KERNEL_SOFTMAX
+    B, H = 2, 4
+    Q, K, V = wl.make_qkv(wl.Workload("t", "causal", B, H, L, 64, M, "bf16", M + L))
+    W, b = favor.orf_draw(31, H, M, 64)
+    W, b = W.astype(np.float32), b.astype(np.float32)
+    q, k, v, Wd, bd = (*(to_dev(x, "bf16") for x in (Q, K, V)), to_dev(W), to_dev(b))
+    ref, _ = favor.attn_causal(Q, K, V, W, b, S64, kernel=kn)
+    err = {}
+    for chunk in (0, 64):
+        # 64-row segments: several of them, so the default is the feature scan; fp32
+        # outputs, so that the output's own rounding does not hide the difference
+        out = fv.attn_causal(q, k, v, Wd, bd, S64, kernel=kn, chunk=chunk, segment=64,
+                             out_dtype=__import__("torch").float32)
+        # rows whose denominator cancels would carry the whole norm: medians over rows
+        d = np.linalg.norm(to_host(out) - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+        err[chunk] = np.median(d)
+    # features and weights share their roundings; the intra-chunk weights' own part
+    # is a few percent of the error, so a tenth covers the sampling of the rows
+    assert err[0] <= 1.1 * err[64], err
