@@ -258,9 +258,9 @@ __device__ __forceinline__ void chunk_features_t(typename Mma<T>::frag (*dst)[2]
 // Gradient of one 16-row block of queries (lane column = query i = row0 + lane % 16;
 // qf, df the query and dout fragments, alpha and u_d of the row), with the
 // aggregate S in LDS (SA rows over value columns, sz its column d), W'' (WA, bq)
-// and the input-gradient matrix WT. INTRA adds g~ += K-hat^T P2 with the chunk's
-// key features KT (row m, k = keys) and P2 packed as B operand (k = keys).
-template <typename T, int M, int KN, bool INTRA>
+// and the input-gradient matrix WT, and the intra-chunk term g~ += K-hat^T P2 with the
+// chunk's key features KT (row m, k = keys) and P2 packed as B operand (k = keys).
+template <typename T, int M, int KN>
 __device__ __forceinline__ void query_grad(
     const typename Mma<T>::frag (*WA)[2][64], const float *bq,
     const typename Mma<T>::frag (*WT)[M / 32][64], const typename Mma<T>::frag (*SA)[2][64],
@@ -291,10 +291,8 @@ __device__ __forceinline__ void query_grad(
       p = P::mma(WA[mb][1][l], qf[1], p);
       f32x4 gt = P::mma(SA[mb][0][l], df[0], f32x4{0.f, 0.f, 0.f, 0.f});
       gt = P::mma(SA[mb][1][l], df[1], gt);
-      if constexpr (INTRA) {
-        gt = P::mma(KT[mb][0][l], pb2[0], gt);
-        gt = P::mma(KT[mb][1][l], pb2[1], gt);
-      }
+      gt = P::mma(KT[mb][0][l], pb2[0], gt);
+      gt = P::mma(KT[mb][1][l], pb2[1], gt);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const float gj = fmaf(szv[j], ud, gt[j]);
@@ -383,18 +381,6 @@ __device__ __forceinline__ void load_row_stats(typename Mma<T>::frag (&of)[2], f
   }
 }
 
-template <typename T, int KN, bool RN>
-__device__ __forceinline__ void row_weights(const typename Mma<T>::frag (&qf)[2],
-                                            const typename Mma<T>::frag (&df)[2],
-                                            const T *__restrict__ Oh,
-                                            const float *__restrict__ rsave_h, int i, int L,
-                                            float cM, float s2half, float &alpha, float &ud) {
-  typename Mma<T>::frag of[2];
-  float rs;
-  load_row_stats<T, RN>(of, rs, Oh, rsave_h, i, L);
-  row_weights_loaded<T, KN, RN>(qf, df, of, rs, i, L, cM, s2half, alpha, ud);
-}
-
 // ------------------------------------------------------------ bidirectional dQ (bf16)
 template <typename T, int M>
 struct DqSmem {
@@ -407,7 +393,12 @@ struct DqSmem {
 };
 
 // Items are (head, tile of 8 waves x TBW x 16 rows), walked persistently over
-// XCD-local ranges; Buf1 [BH][M][65] fp32.
+// XCD-local ranges; Buf1 [BH][M][65] fp32. A wave takes its TBW row blocks through
+// one pass over the features, so every operand read from LDS (12 KB per 32 features)
+// meets all of its rows: with one block at a time those reads alone were half of the
+// kernel. Two blocks fit 256 registers (two waves per SIMD). B4 H8 L8192 M256: dQ
+// 51.8 -> 47.7 us, dK and dV 56.6 -> 52.6; B8 H8 L2047 M128: 23.0 -> 21.6 and 25.0 ->
+// 22.6 us. Loading the next tile's rows ahead measured 45.5 against 43.9 us.
 template <typename T, int M, int KN, bool RN, int TBW>
 __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dq(
     const T *__restrict__ Q, const T *__restrict__ dout, const T *__restrict__ out,
@@ -415,11 +406,15 @@ __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dq(
     const float *__restrict__ bqg, const float *__restrict__ W, const float *__restrict__ buf1,
     T *__restrict__ dQ, float2 *__restrict__ aux, int H, int L, float s, int Mr, float cM,
     float wts, int ntiles, int nitems) {
-  using frag = typename Mma<T>::frag;
+  using P = Mma<T>;
+  using frag = typename P::frag;
+  constexpr bool kDot = KN == kCos;   // sum g~ . q-hat, as k_bwd_row_scan does
+  constexpr float sgn = KN == kCos ? -1.f : 1.f;
   __shared__ DqSmem<T, M> sm;
   const int tid = threadIdx.x;
   const int w = tid >> 6;
-  const int g = (tid & 63) >> 4;
+  const int l = tid & 63;
+  const int g = l >> 4;
   const int c16 = tid & 15;
   const float s2half = 0.5f * s * s;
   int begin, end;
@@ -441,22 +436,78 @@ __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dq(
     const T *Qh = Q + (size_t)bh * L * kD;
     const T *dOh = dout + (size_t)bh * L * kD;
     const T *Oh = out + (size_t)bh * L * kD;
-    const frag none[2] = {};
+    const int i0 = (tile * (kBwdBidirThreads / 64) + w) * 16 * TBW + c16;
+    frag qf[TBW][2], df[TBW][2];
+    float alpha[TBW], ud[TBW];
+    {
+      frag of[TBW][2];
+      float rs[TBW];
+#pragma unroll
+      for (int tb = 0; tb < TBW; ++tb) {
+        load_rows64<T>(qf[tb], Qh, i0 + 16 * tb, L);
+        load_rows64<T>(df[tb], dOh, i0 + 16 * tb, L);
+        load_row_stats<T, RN>(of[tb], rs[tb], Oh, rsave + (size_t)bh * L, i0 + 16 * tb, L);
+      }
+#pragma unroll
+      for (int tb = 0; tb < TBW; ++tb)
+        row_weights_loaded<T, KN, RN>(qf[tb], df[tb], of[tb], rs[tb], i0 + 16 * tb, L, cM, s2half,
+                                      alpha[tb], ud[tb]);
+    }
+    f32x4 dacc[TBW][4];
+    float dot[TBW];
 #pragma unroll
     for (int tb = 0; tb < TBW; ++tb) {
-      const int i = tile * (kBwdBidirThreads / 4) * TBW + 16 * (w * TBW + tb) + c16;
-      frag qf[2], df[2];
-      load_rows64<T>(qf, Qh, i, L);
-      load_rows64<T>(df, dOh, i, L);
-      float alpha, ud;
-      row_weights<T, KN, RN>(qf, df, Oh, rsave + (size_t)bh * L, i, L, cM, s2half, alpha, ud);
-      f32x4 dacc[4];
-      float dot2;
-      query_grad<T, M, KN, false>(sm.WA, sm.bq, sm.WT, sm.SA, sm.sz, nullptr, none, qf, df, alpha,
-                                  ud, s, dacc, dot2);
+      dot[tb] = 0.f;
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) dacc[tb][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll 1
+    for (int sidx = 0; sidx < M / 32; ++sidx) {
+      f32x4 G[TBW][2];
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        const int mb = 2 * sidx + hh;
+        const f32x4 bcv = *reinterpret_cast<const f32x4 *>(&sm.bq[16 * mb + 4 * g]);
+        const f32x4 szv = *reinterpret_cast<const f32x4 *>(&sm.sz[16 * mb + 4 * g]);
+        const frag w0 = sm.WA[mb][0][l], w1 = sm.WA[mb][1][l];
+        const frag a0 = sm.SA[mb][0][l], a1 = sm.SA[mb][1][l];
+#pragma unroll
+        for (int tb = 0; tb < TBW; ++tb) {
+          f32x4 p = P::mma(w0, qf[tb][0], bcv);
+          p = P::mma(w1, qf[tb][1], p);
+          f32x4 gt = P::mma(a0, df[tb][0], f32x4{0.f, 0.f, 0.f, 0.f});
+          gt = P::mma(a1, df[tb][1], gt);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float gj = RN ? fmaf(szv[j], ud[tb], gt[j]) : gt[j];
+            if constexpr (kDot) dot[tb] = fmaf(gj, feature<KN, P>(p[j], bcv[j]), dot[tb]);
+            G[tb][hh][j] = sgn * gj * feature_slope<KN, P>(p[j], bcv[j]);
+          }
+        }
+      }
+      frag gb[TBW];
+#pragma unroll
+      for (int tb = 0; tb < TBW; ++tb) gb[tb] = P::pack(G[tb][0], G[tb][1]);
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) {
+        const frag wt = sm.WT[kb][sidx][l];
+#pragma unroll
+        for (int tb = 0; tb < TBW; ++tb) dacc[tb][kb] = P::mma(wt, gb[tb], dacc[tb][kb]);
+      }
+    }
+#pragma unroll
+    for (int tb = 0; tb < TBW; ++tb) {
+      const int i = i0 + 16 * tb;
+      float d = 0.f;   // g~ . q-hat
+      if constexpr (kDot) {
+        d = dot[tb] + __shfl_xor(dot[tb], 16);
+        d += __shfl_xor(d, 32);
+      }
       if (i < L) {
-        store_qgrad<T, KN>(dQ + ((size_t)bh * L + i) * kD, dacc, qf, alpha, dot2, s);
-        if (g == 0) aux[(size_t)bh * L + i] = make_float2(alpha, alpha * ud);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) dacc[tb][kb] *= alpha[tb];
+        store_qgrad<T, KN>(dQ + ((size_t)bh * L + i) * kD, dacc[tb], qf[tb], alpha[tb], d, s);
+        if (g == 0) aux[(size_t)bh * L + i] = make_float2(alpha[tb], alpha[tb] * ud[tb]);
       }
     }
   }
@@ -645,7 +696,7 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dq_scan(
     }
     f32x4 dacc[4];
     float dot2;
-    query_grad<T, M, KN, true>(sm.WA, sm.bq, sm.WT, sm.SA, sm.sz, sm.KT, pb2, qf, df, alpha, ud,
+    query_grad<T, M, KN>(sm.WA, sm.bq, sm.WT, sm.SA, sm.sz, sm.KT, pb2, qf, df, alpha, ud,
                                s, dacc, dot2, s0, s1);
     if (hf == 1) {
 #pragma unroll
@@ -666,11 +717,11 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dq_scan(
 }
 
 // ------------------------------------------------------------ key-side rows
-// Gradient of one 16-row block of keys (lane column = key j): h = R C_j (+ INTRA_K:
-// Q-hat^T P3 with the chunk's query features QT and P3 packed, k = queries), dK
-// from h; dV = R^T k-hat (+ INTRA_V: u~^T (P4 masked) with the chunk's query
-// features QA and u~^T in UF). KPART / VPART select what is computed.
-template <typename T, int M, int KN, bool KPART, bool VPART, bool INTRA>
+// Gradient of one 16-row block of keys (lane column = key j): h = R C_j + Q-hat^T P3
+// with the chunk's query features QT and P3 packed (k = queries), dK from h;
+// dV = R^T k-hat + u~^T (P4 masked) with the chunk's query features QA and u~^T in
+// UF. KPART / VPART select what is computed.
+template <typename T, int M, int KN, bool KPART, bool VPART>
 __device__ __forceinline__ void key_grad(
     const typename Mma<T>::frag (*WA)[2][64], const float *bq,
     const typename Mma<T>::frag (*WT)[M / 32][64], const typename Mma<T>::frag (*RA)[2][64],
@@ -710,10 +761,8 @@ __device__ __forceinline__ void key_grad(
       if constexpr (KPART) {
         f32x4 hv = P::mma(RA[mb][0][l], vf[0], zero4);
         hv = P::mma(RA[mb][1][l], vf[1], hv);
-        if constexpr (INTRA) {
-          hv = P::mma(QT[mb][0][l], pb3[0], hv);
-          hv = P::mma(QT[mb][1][l], pb3[1], hv);
-        }
+        hv = P::mma(QT[mb][0][l], pb3[0], hv);
+        hv = P::mma(QT[mb][1][l], pb3[1], hv);
         const f32x4 rzv = *reinterpret_cast<const f32x4 *>(&rz[16 * mb + 4 * g]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -732,17 +781,15 @@ __device__ __forceinline__ void key_grad(
       const frag kb_ = P::pack(kh[0], kh[1]);
 #pragma unroll
       for (int nb = 0; nb < 4; ++nb) vacc[nb] = P::mma(RB[nb][sidx][l], kb_, vacc[nb]);
-      if constexpr (INTRA) {
 #pragma unroll
-        for (int qb = 0; qb < 4; ++qb) p4[qb] = P::mma(QA[qb][sidx][l], kb_, p4[qb]);
-      }
+      for (int qb = 0; qb < 4; ++qb) p4[qb] = P::mma(QA[qb][sidx][l], kb_, p4[qb]);
     }
   }
   if constexpr (KPART) {
     doth += __shfl_xor(doth, 16);
     doth += __shfl_xor(doth, 32);
   }
-  if constexpr (VPART && INTRA) {
+  if constexpr (VPART) {
     // keep queries i >= j, then u~^T (q-hat . k-hat)
 #pragma unroll
     for (int qb = 0; qb < 4; ++qb)
@@ -795,16 +842,21 @@ struct DkvSmem {
   frag RB[4][M / 32][64];   // dBuf1 value columns over features
 };
 
+// Tiles and row blocks as in k_bwd_dq.
 template <typename T, int M, int KN, int TBW>
 __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dkv(
     const T *__restrict__ K, const T *__restrict__ V,
     const typename Mma<T>::frag *__restrict__ wfr, const float *__restrict__ bqg,
     const float *__restrict__ W, const float *__restrict__ dbuf1, T *__restrict__ dK,
     T *__restrict__ dV, int H, int L, float s, int Mr, float cM, float wts, int ntiles, int nitems) {
-  using frag = typename Mma<T>::frag;
+  using P = Mma<T>;
+  using frag = typename P::frag;
+  constexpr float sgn = KN == kCos ? -1.f : 1.f;
   __shared__ DkvSmem<T, M> sm;
   const int tid = threadIdx.x;
   const int w = tid >> 6;
+  const int l = tid & 63;
+  const int g = l >> 4;
   const int c16 = tid & 15;
   const float s2half = 0.5f * s * s;
   int begin, end;
@@ -827,23 +879,71 @@ __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dkv(
     }
     const T *Kh = K + (size_t)bh * L * kD;
     const T *Vh = V + (size_t)bh * L * kD;
-    const frag none[2] = {};
+    const int j0 = (tile * (kBwdBidirThreads / 64) + w) * 16 * TBW + c16;
+    frag kf[TBW][2], vf[TBW][2];
+    f32x4 kacc[TBW][4], vacc[TBW][4];
+    float dot[TBW];   // h . k-hat
 #pragma unroll
     for (int tb = 0; tb < TBW; ++tb) {
-      const int j = tile * (kBwdBidirThreads / 4) * TBW + 16 * (w * TBW + tb) + c16;
-      frag kf[2], vf[2];
-      load_rows64<T>(kf, Kh, j, L);
-      load_rows64<T>(vf, Vh, j, L);
-      float D = 1.f;
-      if constexpr (KN == kCos) D = cM * expf(s2half * sq_norm16<T>(kf));
-      f32x4 kacc[4], vacc[4];
-      float doth;
-      key_grad<T, M, KN, true, true, false>(sm.WA, sm.bq, sm.WT, sm.RA, sm.rz, sm.RB, nullptr,
-                                            none, nullptr, nullptr, kf, vf, 0, kacc, doth,
-                                            vacc);
+      load_rows64<T>(kf[tb], Kh, j0 + 16 * tb, L);
+      load_rows64<T>(vf[tb], Vh, j0 + 16 * tb, L);
+      dot[tb] = 0.f;
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb) kacc[tb][nb] = vacc[tb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll 1
+    for (int sidx = 0; sidx < M / 32; ++sidx) {
+      f32x4 kh[TBW][2], G[TBW][2];
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        const int mb = 2 * sidx + hh;
+        const f32x4 bcv = *reinterpret_cast<const f32x4 *>(&sm.bq[16 * mb + 4 * g]);
+        const f32x4 rzv = *reinterpret_cast<const f32x4 *>(&sm.rz[16 * mb + 4 * g]);
+        const frag w0 = sm.WA[mb][0][l], w1 = sm.WA[mb][1][l];
+        const frag a0 = sm.RA[mb][0][l], a1 = sm.RA[mb][1][l];
+#pragma unroll
+        for (int tb = 0; tb < TBW; ++tb) {
+          f32x4 p = P::mma(w0, kf[tb][0], bcv);
+          p = P::mma(w1, kf[tb][1], p);
+          f32x4 hv = P::mma(a0, vf[tb][0], rzv);
+          hv = P::mma(a1, vf[tb][1], hv);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            kh[tb][hh][j] = feature<KN, P>(p[j], bcv[j]);
+            if constexpr (KN == kCos) dot[tb] = fmaf(hv[j], kh[tb][hh][j], dot[tb]);
+            G[tb][hh][j] = sgn * hv[j] * feature_slope<KN, P>(p[j], bcv[j]);
+          }
+        }
+      }
+      frag gb[TBW], hb[TBW];
+#pragma unroll
+      for (int tb = 0; tb < TBW; ++tb) {
+        gb[tb] = P::pack(G[tb][0], G[tb][1]);
+        hb[tb] = P::pack(kh[tb][0], kh[tb][1]);
+      }
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb) {
+        const frag wt = sm.WT[nb][sidx][l];
+        const frag rb = sm.RB[nb][sidx][l];
+#pragma unroll
+        for (int tb = 0; tb < TBW; ++tb) {
+          kacc[tb][nb] = P::mma(wt, gb[tb], kacc[tb][nb]);
+          vacc[tb][nb] = P::mma(rb, hb[tb], vacc[tb][nb]);
+        }
+      }
+    }
+#pragma unroll
+    for (int tb = 0; tb < TBW; ++tb) {
+      const int j = j0 + 16 * tb;
+      float D = 1.f, d = 0.f;
+      if constexpr (KN == kCos) {
+        D = cM * expf(s2half * sq_norm16<T>(kf[tb]));
+        d = dot[tb] + __shfl_xor(dot[tb], 16);
+        d += __shfl_xor(d, 32);
+      }
       if (j < L) {
-        store_kgrad<T, KN>(dK + ((size_t)bh * L + j) * kD, kacc, kf, D, doth, s);
-        store_vgrad<T>(dV + ((size_t)bh * L + j) * kD, vacc, D);
+        store_kgrad<T, KN>(dK + ((size_t)bh * L + j) * kD, kacc[tb], kf[tb], D, d, s);
+        store_vgrad<T>(dV + ((size_t)bh * L + j) * kD, vacc[tb], D);
       }
     }
   }
@@ -1085,7 +1185,7 @@ __global__ __launch_bounds__(kScanThreads) void k_bwd_dkv_scan(
     // the tables of the other part are one-element placeholders, never read
     using T2 = const frag(*)[2][64];
     using TS = const frag(*)[M / 32][64];
-    key_grad<T, M, KN, KPART, !KPART, true>(
+    key_grad<T, M, KN, KPART, !KPART>(
         sm.WA, sm.bq, reinterpret_cast<TS>(&sm.WT[0][0][0]), reinterpret_cast<T2>(&sm.RA[0][0][0]),
         sm.rz, reinterpret_cast<TS>(&sm.RB[0][0][0]), sm.QT, pb3,
         reinterpret_cast<TS>(&sm.QA[0][0][0]), sm.UF, kf, vf, 16 * qb + c16, kacc, doth,
@@ -1132,8 +1232,7 @@ static float wt_scale(const Shape &sh) {
   return sh.kernel == 1 ? sh.s / sqrtf((float)sh.Mr) : sh.s;
 }
 
-// Rows per persistent bidirectional tile: 8 waves x kBwdTbw blocks of 16 (one
-// block per call of the row functions).
+// Rows per persistent bidirectional tile: 8 waves x kBwdTbw blocks of 16.
 constexpr int kBwdTbw = 2;
 constexpr int kBwdMaxWorkgroups = 256;
 
