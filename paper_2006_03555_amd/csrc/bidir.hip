@@ -554,7 +554,7 @@ static hipError_t kside_kernel(const Shape &sh, Dt in, const void *K, const void
                                const float2 *aux) {
 #define FAVOR_KSIDE(T, MM, NG) \
   kside_launch<T, MM, NG, KN, AGG>(sh, K, V, W, b, wfr, bq, part, rows_per_split, nsplit, st, aux)
-  if (nsplit * sh.BH < kKsideFeatureGroupBelow && sh.M > 64) {
+  if (kside_grouped(in, sh.M, nsplit * sh.BH)) {
     if (in == Dt::BF16)
       FAVOR_KSIDE(bf16, 64, 1);
     else

@@ -62,15 +62,16 @@ constexpr int kMinRowsPerSplit = 256;
 // L <= 1024 for 32 heads; longer sequences keep the workgroup target's segments)
 constexpr int kMinRowsPerSegment = 128;
 // Rows per key-pass split at least, for the bidirectional call. A split of 256
-// rows amortises a workgroup's W'' build; while the chip is not full even with
-// one workgroup per 64 features of a split (favor::kKsideFeatureGroupBelow),
-// shorter splits take less time in spite of it. float32 B1 H1 L1024 M128, whole
-// call: 37.5 us with 256-row splits, 30.2 with 128, 27.1 with 64; B2 H8 L1024
-// M256 (full at 256 rows): 51.8, 57.0, 57.4.
+// rows amortises a workgroup's W'' build; while half of the CUs would be idle even
+// with one workgroup per 64 features of a split (favor::kside_grouped), shorter
+// splits take less time in spite of it. float32 B1 H1 L1024 M128, whole call: 37.5
+// us with 256-row splits, 30.2 with 128, 27.1 with 64; B2 H8 L1024 M256 (full at
+// 256 rows): 51.8, 57.0, 57.4; bf16 B1 H12 L2500 M128 (nearly full at 256 rows):
+// 22.3 with 256, 24.9 with 128.
 int min_split_rows(int BH, int tiles, int M) {
   int rows = kMinRowsPerSplit;
-  while (rows > 64 && (long long)BH * ((tiles + rows / 64 - 1) / (rows / 64)) * (M / 64) <
-                          favor::kKsideFeatureGroupBelow)
+  while (rows > 64 && (long long)BH * ((tiles + rows / 64 - 1) / (rows / 64)) * (M / 64) <=
+                          favor::kKsideGroupSplits)
     rows /= 2;
   return rows;
 }

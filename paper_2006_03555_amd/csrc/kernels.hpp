@@ -65,11 +65,16 @@ hipError_t launch_feature_map(const Shape &sh, Dt in, Dt out, const void *X, con
 // one partial per row range): bf16 inputs with M >= 128 use two.
 constexpr int kside_groups(Dt in, int M) { return in == Dt::BF16 && M >= 128 ? 2 : 1; }
 
-// Launches of k_kside with fewer (head, row split) pairs than this, a workgroup
-// per CU, run one workgroup per 64 features of a split instead of one per split.
-// float32 B2 H8 L1024 M256 (64 pairs): 80.2 -> 51.8 us for the whole call; bf16
-// B4 H8 L1024 M256 (128 pairs): 28.7 -> 26.5 us.
-constexpr int kKsideFeatureGroupBelow = 256;
+// The key pass runs one workgroup per 64 features of a row split (rather than one
+// per split) while there are at most this many splits: one per CU in twice as many
+// workgroups. Measured around the line (k_kside, us, grouped / not): fp32 M 256, 128
+// splits 42 / 55, 192 splits 61 / 55; fp32 M 128, 128 splits 25 / 33, 192 splits 42 /
+// 33; bf16 M 128, 128 splits 12.8 / 13.0, 192 splits 15.4 / 14.8. bf16 M 256 gains up
+// to the CU count (192 splits 17.7 / 18.7, 228 splits 17.7 / 19.0).
+constexpr int kKsideGroupSplits = 128;
+inline bool kside_grouped(Dt in, int M, int splits) {
+  return M > 64 && splits <= (in == Dt::BF16 && M == 256 ? 255 : kKsideGroupSplits);
+}
 
 // K side: per (head, row range) partial Buf1 = K'^T [V 1] -> part [BH][nsplit][M][65].
 // Builds W'' = (s / 2 pi) W from W, b itself and stores the fragments
