@@ -62,17 +62,30 @@ constexpr int kMinRowsPerSplit = 256;
 // L <= 1024 for 32 heads; longer sequences keep the workgroup target's segments)
 constexpr int kMinRowsPerSegment = 128;
 // Rows per key-pass split at least, for the bidirectional call. A split of 256
-// rows amortises a workgroup's W'' build; while half of the CUs would be idle even
-// with one workgroup per 64 features of a split (favor::kside_grouped), shorter
-// splits take less time in spite of it. float32 B1 H1 L1024 M128, whole call: 37.5
-// us with 256-row splits, 30.2 with 128, 27.1 with 64; B2 H8 L1024 M256 (full at
-// 256 rows): 51.8, 57.0, 57.4; bf16 B1 H12 L2500 M128 (nearly full at 256 rows):
-// 22.3 with 256, 24.9 with 128.
-int min_split_rows(int BH, int tiles, int M) {
+// rows amortises a workgroup's W'' build; while most CUs would be idle, shorter
+// splits take less time in spite of it, as long as the reduction, which walks a
+// head's splits in series, does not take longer than they save. Whole calls (us)
+// with splits of 256 / 128 / 64 rows:
+//   fp32, halved while the splits number at most kKsideGroupSplits workgroups and
+//   a head then has no more splits than a split has rows: B1 H1 L1024 M128 27.1 /
+//   19.5 / 17.8, B1 H8 L1024 M256 33.3 / 27.7 / 32.3, B1 H1 M64 L4096 28.2 / 21.6 /
+//   20.9, L8192 30.5 / 25.8 / 28.4, L16384 35.0 / 33.6 / 43.3, L32768 46.7 / 52.5 / 79.3
+//   bf16, a quarter of the time per tile, so at most 16 splits per head and as many
+//   workgroups (twice that at M = 256) as a split has rows: B1 H1 M64 L512 11.4 / 9.7 /
+//   9.2, L2048 11.9 / 10.8 / 11.6, L4096 12.6 / 12.6 / 15.0, L16384 18.5 / 23.2 / 35.9; B1 H8
+//   M128 L256 11.7 / 10.2 / 9.9, L512 12.1 / 10.8 / 11.4, L2048 15.9 / 17.1 / 23.4; B1 H16
+//   L512 M256 15.1 / 14.8 / 17.5
+int min_split_rows(int BH, int tiles, int M, bool bf16) {
+  const auto splits = [&](int rows) { return (tiles + rows / 64 - 1) / (rows / 64); };
+  const auto groups = [&](int rows) { return (long long)BH * splits(rows) * (M / 64); };
   int rows = kMinRowsPerSplit;
-  while (rows > 64 && (long long)BH * ((tiles + rows / 64 - 1) / (rows / 64)) * (M / 64) <=
-                          favor::kKsideGroupSplits)
-    rows /= 2;
+  while (rows > 64) {
+    const int half = rows / 2;
+    if (bf16 ? splits(half) > 16 || groups(half) > (M == 256 ? 2 * half : half)
+             : splits(half) > half || groups(rows) > favor::kKsideGroupSplits)
+      break;
+    rows = half;
+  }
   return rows;
 }
 // Longest sequence per head (and longest causal segment): the kernels index
@@ -221,7 +234,8 @@ Plan make_plan(const favor_desc *g, int op) {
                                                      : kCausalWorkgroups;
     int want = (target + p.BH - 1) / p.BH;
     const int min_rows =
-        causal ? kMinRowsPerSegment : min_split_rows(p.BH, tiles, padded_m(g->M));
+        causal ? kMinRowsPerSegment
+               : min_split_rows(p.BH, tiles, padded_m(g->M), in == favor::Dt::BF16);
     int max_split = tiles / (min_rows / 64);
     if (max_split < 1) max_split = 1;
     if (want > max_split) want = max_split;
