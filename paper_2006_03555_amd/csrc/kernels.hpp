@@ -66,14 +66,18 @@ hipError_t launch_feature_map(const Shape &sh, Dt in, Dt out, const void *X, con
 constexpr int kside_groups(Dt in, int M) { return in == Dt::BF16 && M >= 128 ? 2 : 1; }
 
 // The key pass runs one workgroup per 64 features of a row split (rather than one
-// per split) while there are at most this many splits: one per CU in twice as many
-// workgroups. Measured around the line (k_kside, us, grouped / not): fp32 M 256, 128
-// splits 42 / 55, 192 splits 61 / 55; fp32 M 128, 128 splits 25 / 33, 192 splits 42 /
-// 33; bf16 M 128, 128 splits 12.8 / 13.0, 192 splits 15.4 / 14.8. bf16 M 256 gains up
-// to the CU count (192 splits 17.7 / 18.7, 228 splits 17.7 / 19.0).
+// per split) while there are few splits: at most this many, one per CU in twice as
+// many workgroups. Whole bidirectional calls around the line (us, grouped / not): fp32
+// M 256, 128 splits (B1 H8 L4096) 71.6 / 83.1, 144 splits (H12 L3072) 112.7 / 105.7; fp32
+// M 128, the same calls 44.1 / 52.3 and 69.7 / 60.4; bf16 M 128 21.6 / 21.9 and 23.6 / 22.8.
+// bf16 M 256 runs two row groups per ungrouped workgroup, so a split's four grouped
+// ones fill the chip one and a half times: 192 splits (H3 L16384) 33.5 / 34.4, (H24
+// L2048) 30.6 / 31.1, but 200 (H5 L10240) 34.6 / 32.6, 240 (H12 L5120) 34.9 / 32.1.
 constexpr int kKsideGroupSplits = 128;
+constexpr int kKsideGroupSplitsBf16M256 = 192;
 inline bool kside_grouped(Dt in, int M, int splits) {
-  return M > 64 && splits <= (in == Dt::BF16 && M == 256 ? 255 : kKsideGroupSplits);
+  return M > 64 &&
+         splits <= (in == Dt::BF16 && M == 256 ? kKsideGroupSplitsBf16M256 : kKsideGroupSplits);
 }
 
 // K side: per (head, row range) partial Buf1 = K'^T [V 1] -> part [BH][nsplit][M][65].
