@@ -1298,12 +1298,26 @@ static hipError_t causal_typed(const Shape &sh, const void *Q, const void *K, co
   });
 }
 
+bool causal_solo(const Shape &sh, Dt in, int nseg) {
+  return nseg == 1 && in == Dt::BF16 && !(sh.chunk == 32 && sh.M > 128);
+}
+
+// Whether a causal scan runs as k_out_scan. Not where causal_solo holds: there the
+// causal call's one launch is k_causal_fs, and the calls that run the scan from a
+// prefix of their own (both directions, a backward call recomputing the output and
+// the row scales) give the same bits only by running the same kernel. (k_out_scan
+// would be the faster one there: both directions of B40 H8 L2048 M256 389 us, with
+// k_causal_fs 422, as before k_out_scan.)
+static bool takes_out_scan(const Shape &sh, Dt in, int nseg) {
+  return in == Dt::BF16 && sh.feature_scan && !causal_solo(sh, in, nseg);
+}
+
 hipError_t launch_causal_save(const Shape &sh, Dt in, const void *Q, const void *K,
                               const void *V, const void *wfr, const float *bq,
                               const float *prefix, void *o, float *rsave, int seg_len, int nseg,
                               float *halves, hipStream_t st) {
   if (!sh.renorm) return hipErrorInvalidValue;
-  if (in == Dt::BF16 && sh.feature_scan)
+  if (takes_out_scan(sh, in, nseg))
     return launch_out_scan(sh, Dt::BF16, Q, K, V, wfr, bq, prefix, o, rsave, seg_len, nseg, st);
   if (in == Dt::BF16)
     return causal_fs_typed<bf16, true>(sh, Q, K, V, wfr, bq, prefix, o, seg_len, nseg, st, rsave);
@@ -1314,7 +1328,7 @@ hipError_t launch_causal_save(const Shape &sh, Dt in, const void *Q, const void 
 hipError_t launch_causal(const Shape &sh, Dt in, Dt out, const void *Q, const void *K,
                          const void *V, const void *wfr, const float *bq, const float *prefix,
                          void *o, int seg_len, int nseg, float *halves, hipStream_t st) {
-  if (in == Dt::BF16 && sh.feature_scan)
+  if (takes_out_scan(sh, in, nseg))
     return launch_out_scan(sh, out, Q, K, V, wfr, bq, prefix, o, nullptr, seg_len, nseg, st);
   if (in == Dt::BF16)
     return out == Dt::BF16
@@ -1324,10 +1338,6 @@ hipError_t launch_causal(const Shape &sh, Dt in, Dt out, const void *Q, const vo
                                                      nseg, st, halves)
                          : causal_typed<float, float>(sh, Q, K, V, wfr, bq, prefix, o, seg_len,
                                                       nseg, st, halves);
-}
-
-bool causal_solo(const Shape &sh, Dt in, int nseg) {
-  return nseg == 1 && in == Dt::BF16 && !(sh.chunk == 32 && sh.M > 128);
 }
 
 hipError_t launch_causal_solo(const Shape &sh, Dt out, const void *Q, const void *K,

@@ -30,8 +30,8 @@ struct Shape {
   float keps;    // ReLU: added to every feature
   int chunk;     // tokens per step of the causal scan: 64, or 32 (bf16 inputs)
   // causal scan of bf16 inputs: k_out_scan (64-token chunks, products over all
-  // features through LDS) where the caller leaves the chunk length to the library,
-  // k_causal_fs with `chunk` where it names one. Per launch (us): B4 H8 L8192 M256
+  // features through LDS) where the caller leaves the chunk length to the library and
+  // a head has several segments, else k_causal_fs with `chunk`. Per launch (us): B4 H8 L8192 M256
   // 71.7 against 82.1 (T = 64), B1 H16 L65536 M256 289 against 311, B8 H8 L2047
   // M128 25.4 against 27.6 (T = 32). Whole calls: both directions of B4 H8 L8192
   // 161 -> 151, B1 H16 L65536 389 -> 354.

@@ -76,3 +76,34 @@ def test_backward_reads_its_workspace(M):
     c = fv.attn_causal_backward(q, k, v, Wd, bd, S64, do, state_in=s0, return_state_grad=True,
                                 out=out, row_scale=rs)
     assert all(torch.equal(x, y) for x, y in zip(a, c))
+
+
+# the default chunk length, one segment by length and by head count
+@pytest.mark.parametrize("B,H,L", [(2, 2, 150), (1, 2, 127), (65, 8, 200)])
+@pytest.mark.parametrize("M", [64, 112, 256])
+@pytest.mark.parametrize("kernel", ["softmax", "relu"])
+def test_every_call_runs_the_same_scan(B, H, L, M, kernel):
+    """The causal half of attn_both is bitwise what attn_causal returns, and a backward
+    call that recomputes the output and the row scales returns the bits it returns when
+    given those of the forward call."""
+    import torch
+    fv = __import__("paper_2006_03555_amd")
+    kw = dict(kernel=favor.KERNEL_RELU if kernel == "relu" else favor.KERNEL_SOFTMAX)
+    Q, K, V = wl.make_qkv(wl.Workload("t", "causal", B, H, L, 64, M, "bf16", 6))
+    W, b = favor.orf_draw(25, H, M, 64)
+    q, k, v = (to_dev(x, "bf16") for x in (Q, K, V))
+    args = (q, k, v, to_dev(W), to_dev(b), S64)
+    do, db = (to_dev(np.random.default_rng(i).standard_normal(Q.shape), "bf16") for i in (1, 2))
+    rs, rb, rc = (torch.empty((B, H, L), device="cuda") for _ in range(3))
+    _, s0 = fv.attn_causal(k, q, v, *args[3:], return_state=True, **kw)
+    out = fv.attn_causal(*args, state_in=s0, row_scale=rs, **kw)
+    ob, oc = fv.attn_both(*args, state_in=s0, row_scale_bidir=rb, row_scale_causal=rc, **kw)
+    assert torch.equal(out, oc) and torch.equal(rs, rc)
+    kw.update(state_in=s0, return_state_grad=True)
+    saved = fv.attn_causal_backward(*args, do, out=out, row_scale=rs, **kw)
+    fresh = fv.attn_causal_backward(*args, do, **kw)
+    assert all(torch.equal(x, y) for x, y in zip(saved, fresh))
+    saved = fv.attn_both_backward(*args, db, do, out_bidir=ob, row_scale_bidir=rb, out_causal=oc,
+                                  row_scale_causal=rc, **kw)
+    fresh = fv.attn_both_backward(*args, db, do, **kw)
+    assert all(torch.equal(x, y) for x, y in zip(saved, fresh))
