@@ -70,11 +70,14 @@ def test_64_token_scan_fits_one_workgroup_per_cu(descriptors):
         assert LDS_PER_CU // 2 < f["group_segment_fixed_size"] <= LDS_PER_CU, name
 
 
-def test_gradient_kernels_keep_off_scratch(tmp_path_factory):
+# the bf16 causal gradients' file is feature_scan.hip (test_causal_gradient_scans_fit)
+@pytest.mark.parametrize("source", ["backward.hip", "backward_f32.hip"])
+def test_gradient_kernels_keep_off_scratch(tmp_path_factory, source):
     """Every instantiation of the gradient kernels (both feature kinds, bf16 and
     fp32, every M) holds its registers without scratch: at M = 64 the feature
-    loop stays rolled, which a full unroll would spill."""
-    kernels = _kernel_descriptors(tmp_path_factory, "backward.hip")
+    loop stays rolled, which a full unroll would spill, and the fp32 kernels form
+    the lane's offsets once per head."""
+    kernels = _kernel_descriptors(tmp_path_factory, source)
     assert kernels
     spilled = {n: f["private_segment_fixed_size"] for n, f in kernels.items()
                if f["private_segment_fixed_size"] > 0}
