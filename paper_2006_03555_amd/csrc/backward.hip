@@ -398,7 +398,10 @@ struct DqSmem {
 // meets all of its rows: with one block at a time those reads alone were half of the
 // kernel. Two blocks fit 256 registers (two waves per SIMD). B4 H8 L8192 M256: dQ
 // 51.8 -> 47.7 us, dK and dV 56.6 -> 52.6; B8 H8 L2047 M128: 23.0 -> 21.6 and 25.0 ->
-// 22.6 us. Loading the next tile's rows ahead measured 45.5 against 43.9 us.
+// 22.6 us. Loading the next tile's rows ahead measured 45.5 against 43.9 us. The two
+// feature steps of M = 64 are unrolled: rolled, they were slower than one block at a
+// time (training step of B8 H8 L2047: one block 77.6 us, rolled 79.8, unrolled 78.1;
+// ReLU 72.8, 74.3, 73.9).
 template <typename T, int M, int KN, bool RN, int TBW>
 __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dq(
     const T *__restrict__ Q, const T *__restrict__ dout, const T *__restrict__ out,
@@ -461,7 +464,7 @@ __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dq(
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) dacc[tb][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-#pragma unroll 1
+#pragma unroll (M == 64 ? 2 : 1)
     for (int sidx = 0; sidx < M / 32; ++sidx) {
       f32x4 G[TBW][2];
 #pragma unroll
@@ -891,7 +894,7 @@ __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dkv(
 #pragma unroll
       for (int nb = 0; nb < 4; ++nb) kacc[tb][nb] = vacc[tb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-#pragma unroll 1
+#pragma unroll (M == 64 ? 2 : 1)
     for (int sidx = 0; sidx < M / 32; ++sidx) {
       f32x4 kh[TBW][2], G[TBW][2];
 #pragma unroll

@@ -17,7 +17,7 @@ S64 = 64 ** -0.25
 
 
 @pytest.mark.parametrize("kind", list(KINDS))
-@pytest.mark.parametrize("M", [80, 128, 208, 256])
+@pytest.mark.parametrize("M", [64, 80, 128, 208, 256])
 @pytest.mark.parametrize("L", [1, 16, 17, 33, 255, 257])
 def test_block_edges(kind, M, L):
     import torch
