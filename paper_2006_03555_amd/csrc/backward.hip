@@ -381,7 +381,7 @@ __device__ __forceinline__ void load_row_stats(typename Mma<T>::frag (&of)[2], f
   }
 }
 
-// ------------------------------------------------------------ bidirectional dQ (bf16)
+// ------------------------------------------------------------ bidirectional dQ
 template <typename T, int M>
 struct DqSmem {
   using frag = typename Mma<T>::frag;
@@ -394,9 +394,10 @@ struct DqSmem {
 
 // Items are (head, tile of 8 waves x TBW x 16 rows), walked persistently over
 // XCD-local ranges; Buf1 [BH][M][65] fp32. A wave takes its TBW row blocks through
-// one pass over the features, so every operand read from LDS (12 KB per 32 features)
-// meets all of its rows: with one block at a time those reads alone were half of the
-// kernel. Two blocks fit 256 registers (two waves per SIMD). B4 H8 L8192 M256: dQ
+// one pass over the features. fp32 takes one block (see f32_dq_tiles), bf16 two, so
+// every operand read from LDS (12 KB per 32 features) meets both: with one block at a
+// time those reads alone were half of the bf16 kernel. Two blocks fit 256 registers
+// (two waves per SIMD). B4 H8 L8192 M256: dQ
 // 51.8 -> 47.7 us, dK and dV 56.6 -> 52.6; B8 H8 L2047 M128: 23.0 -> 21.6 and 25.0 ->
 // 22.6 us. Loading the next tile's rows ahead measured 45.5 against 43.9 us. The two
 // feature steps of M = 64 are unrolled: rolled, they were slower than one block at a
@@ -1305,23 +1306,40 @@ static hipError_t causal_dq_f32(const Shape &sh, const BwdArgs &a, hipStream_t s
   });
 }
 
-static hipError_t bidir_dq_bf16(const Shape &sh, const BwdArgs &a, hipStream_t st) {
-  using T = bf16;
-  const int rows = kBwdBidirThreads / 4 * kBwdTbw;
+template <typename T, int M, int TBW>
+static hipError_t bidir_dq(const Shape &sh, const BwdArgs &a, hipStream_t st) {
+  const int rows = kBwdBidirThreads / 4 * TBW;
   const int ntiles = (sh.L + rows - 1) / rows;
   const int nitems = ntiles * sh.BH;
   dim3 grid(min(nitems, kBwdMaxWorkgroups));
   return bwd_variant(sh, [&](auto kn, auto rn) -> hipError_t {
     constexpr int KN = decltype(kn)::value;
     constexpr bool RN = decltype(rn)::value;
-    FAVOR_BWD_DISPATCH_M(sh.M,
-        hipLaunchKernelGGL((k_bwd_dq<T, MM, KN, RN, kBwdTbw>), grid, dim3(kBwdBidirThreads), 0,
-                           st, (const T *)a.Q, (const T *)a.dout, (const T *)a.out, a.rsave,
-                           (const Mma<T>::frag *)a.wfr, a.bq, a.W, a.state, (T *)a.dQ, a.aux,
-                           sh.H, sh.L, sh.s, sh.Mr, feature_norm(sh), wt_scale(sh), ntiles,
-                           nitems));
+    hipLaunchKernelGGL((k_bwd_dq<T, M, KN, RN, TBW>), grid, dim3(kBwdBidirThreads), 0, st,
+                       (const T *)a.Q, (const T *)a.dout, (const T *)a.out, a.rsave,
+                       (const typename Mma<T>::frag *)a.wfr, a.bq, a.W, a.state, (T *)a.dQ,
+                       a.aux, sh.H, sh.L, sh.s, sh.Mr, feature_norm(sh), wt_scale(sh), ntiles,
+                       nitems);
     return hipGetLastError();
   });
+}
+
+static hipError_t bidir_dq_bf16(const Shape &sh, const BwdArgs &a, hipStream_t st) {
+  FAVOR_BWD_DISPATCH_M(sh.M, return bidir_dq<bf16, MM, kBwdTbw>(sh, a, st));
+}
+
+// fp32 dQ with M <= 128 by tiles of 128 rows and one workgroup per CU (k_bwd_dq, its
+// operands in LDS) where the tiles are at least nine tenths full and give every CU
+// the same number: it then takes less time per row than k_bwd_dq_f32, whose waves hold
+// the operands and each load every row. Forward and backward (us), k_bwd_dq_f32 / this
+// one: cos features M128 B4 H8 L2048 193.9 / 186.2, B8 H8 L4096 636.6 / 616.1, B6 H8
+// L4000 533.4 / 522.0, and three quarters full, B3 H8 L2048, 173.6 / 177.9; ReLU M64 B2
+// H8 L2048 86.4 / 83.0, B8 H8 L4096 374.6 / 365.2.
+static bool f32_dq_tiles(const Shape &sh) {
+  const long long rows = kBwdBidirThreads / 4;
+  const long long tiles = sh.BH * ((sh.L + rows - 1) / rows);
+  const long long rounds = (tiles + kBwdMaxWorkgroups - 1) / kBwdMaxWorkgroups;
+  return sh.M <= 128 && 10LL * sh.BH * sh.L >= 9 * rounds * kBwdMaxWorkgroups * rows;
 }
 
 hipError_t launch_bwd_dq(const Shape &sh, Dt in, bool causal, const BwdArgs &a, hipStream_t st,
@@ -1329,7 +1347,10 @@ hipError_t launch_bwd_dq(const Shape &sh, Dt in, bool causal, const BwdArgs &a, 
   if (causal)
     return in == Dt::BF16 ? launch_bwd_dq_scan(sh, a, accumulate, st)
                           : causal_dq_f32(sh, a, st, accumulate);
-  return in == Dt::BF16 ? bidir_dq_bf16(sh, a, st) : launch_bwd_dq_f32(sh, a, st);
+  if (in == Dt::BF16) return bidir_dq_bf16(sh, a, st);
+  if (f32_dq_tiles(sh))
+    return sh.M == 64 ? bidir_dq<float, 64, 1>(sh, a, st) : bidir_dq<float, 128, 1>(sh, a, st);
+  return launch_bwd_dq_f32(sh, a, st);
 }
 
 static hipError_t causal_dkv_f32(const Shape &sh, const BwdArgs &a, hipStream_t st) {

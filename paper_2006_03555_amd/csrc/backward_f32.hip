@@ -10,7 +10,12 @@
 // them; what a launch of few rows (B2 H8 L1024: 1024 row blocks) needs is all CUs
 // at work and no chain of feature steps. Walking a 256-row tile per workgroup with
 // the operand tables in LDS, 128 features at a time, took 2 x 39 us (dQ) and 2 x
-// 48 us (dK, dV) there on 64 workgroups.
+// 48 us (dK, dV) there on 64 workgroups. (dQ of M <= 128 with enough rows to give every
+// CU full tiles takes that form all the same: f32_dq_tiles in backward.hip.)
+// A block's rows are loaded while the block before is worked on, each tensor's once
+// that block's fragments of it are dead: loaded together after them, one third of the
+// block before their use, many rows took longer (forward and backward of B8 H8 L4096
+// cos M256 1220 us, now 1180; B2 H8 L1024 123.0, now 123.6).
 #include <type_traits>
 
 #include "favor_common.hpp"
@@ -147,44 +152,54 @@ __global__ __launch_bounds__(64 * f32_waves(M), 2) void k_bwd_dq_f32(
     RowOps op;
     load_row_ops(op, wfr + (size_t)h * (M / 16) * 128, bqg + (size_t)h * M,
                  W + (size_t)h * Mr * kD, buf1 + (size_t)bh * M * 65, w, Mr, wts);
-    // a block's rows are loaded while the block before is contracted and stored
+    // a block's rows are loaded while the block before is worked on, each tensor's as
+    // soon as that block's fragments are read for the last time
     f32x8 qf[2], df[2], of[2];
     float rs = 0.f;
-    auto load_block = [&](int item) __attribute__((always_inline)) {
+    auto load_out = [&](int item) __attribute__((always_inline)) {
       const int t = (item - bh * ntiles) * 16 + c16;
-      load_rows16(qf, Q + (size_t)bh * L * kD, t, L);
-      load_rows16(df, dout + (size_t)bh * L * kD, t, L);
       if constexpr (RN) {
         load_rows16(of, out + (size_t)bh * L * kD, t, L);
         rs = t < L ? rsave[(size_t)bh * L + t] : 0.f;
       }
     };
-    load_block(first);
+    load_out(first);
+    load_rows16(df, dout + (size_t)bh * L * kD, (first - bh * ntiles) * 16 + c16, L);
+    load_rows16(qf, Q + (size_t)bh * L * kD, (first - bh * ntiles) * 16 + c16, L);
     for (int item = first; item < last; ++item) {
       const int t = (item - bh * ntiles) * 16 + c16;
       const int buf = item & 1;
-      float alpha, ud = 0.f, cx = 0.f;   // cx: s^2 g~ . q-hat
+      const bool more = item + 1 < last;
+      float alpha = 1.f, ud = 0.f, cx = 0.f;   // cx: s^2 g~ . q-hat
       if constexpr (RN) {
         alpha = rs;
         ud = -dot_rows(df, of);
-      } else {
-        alpha = KN == kCos ? cM * expf(s2half * dot_rows(qf, qf)) : 1.f;
+        if (more) load_out(item + 1);
       }
       f32x4 G[2];
       float dot = 0.f;
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
-        f32x4 p = Pf::mma(op.wf[hh][0], qf[0], op.bx[hh]);
-        p = Pf::mma(op.wf[hh][1], qf[1], p);
-        f32x4 gt = Pf::mma(op.sa[hh][0], df[0], zero4);
-        gt = Pf::mma(op.sa[hh][1], df[1], gt);
+        G[hh] = Pf::mma(op.sa[hh][0], df[0], zero4);
+        G[hh] = Pf::mma(op.sa[hh][1], df[1], G[hh]);
+      }
+      if (more) load_rows16(df, dout + (size_t)bh * L * kD, t + 16, L);
+      if constexpr (KN == kCos && !RN) alpha = cM * expf(s2half * dot_rows(qf, qf));
+      f32x4 p[2];
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        p[hh] = Pf::mma(op.wf[hh][0], qf[0], op.bx[hh]);
+        p[hh] = Pf::mma(op.wf[hh][1], qf[1], p[hh]);
+      }
+      if (more) load_rows16(qf, Q + (size_t)bh * L * kD, t + 16, L);
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float gj = fmaf(op.sz[hh][j], ud, gt[j]);
-          if constexpr (kDot) dot = fmaf(gj, feature<KN, Pf>(p[j], op.bx[hh][j]), dot);
-          G[hh][j] = sgn * gj * feature_slope<KN, Pf>(p[j], op.bx[hh][j]);
+          const float gj = fmaf(op.sz[hh][j], ud, G[hh][j]);
+          if constexpr (kDot) dot = fmaf(gj, feature<KN, Pf>(p[hh][j], op.bx[hh][j]), dot);
+          G[hh][j] = sgn * gj * feature_slope<KN, Pf>(p[hh][j], op.bx[hh][j]);
         }
-      }
       // the columns of x this wave's sums are finished with
       constexpr int NU = NW >= 4 ? 1 : 4 / NW;
       f32x4 q4[NU];
@@ -193,7 +208,6 @@ __global__ __launch_bounds__(64 * f32_waves(M), 2) void k_bwd_dq_f32(
         for (int k = 0; k < NU; ++k)
           q4[k] = load_quad(Q + (size_t)bh * L * kD, t, L, (w + k * NW) & 3);
       }
-      if (item + 1 < last) load_block(item + 1);
       const f32x8 gb = Pf::pack(G[0], G[1]);
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) red[buf][w][kb][l] = Pf::mma(op.wt[kb], gb, zero4);
@@ -264,34 +278,39 @@ __global__ __launch_bounds__(64 * f32_waves(M), 2) void k_bwd_dkv_f32(
           v[i] = R[(size_t)(32 * w + 16 * (i >> 2) + 4 * g + (i & 3)) * 65 + 16 * nb + c16];
         rb[nb] = Pf::from_f32(v, 1.f);
       }
-    // a block's rows are loaded while the block before is contracted and stored
+    // a block's rows are loaded as k_bwd_dq_f32 does
     f32x8 kf[2], vf[2];
-    auto load_block = [&](int item) __attribute__((always_inline)) {
-      const int t = (item - bh * ntiles) * 16 + c16;
-      load_rows16(kf, K + (size_t)bh * L * kD, t, L);
-      load_rows16(vf, V + (size_t)bh * L * kD, t, L);
-    };
-    load_block(first);
+    load_rows16(vf, V + (size_t)bh * L * kD, (first - bh * ntiles) * 16 + c16, L);
+    load_rows16(kf, K + (size_t)bh * L * kD, (first - bh * ntiles) * 16 + c16, L);
     for (int item = first; item < last; ++item) {
       const int t = (item - bh * ntiles) * 16 + c16;
       const int buf = item & 1;
-      float D = 1.f;
-      if constexpr (KN == kCos) D = cM * expf(s2half * dot_rows(kf, kf));
+      const bool more = item + 1 < last;
       f32x4 kh[2], G[2];
       float dot = 0.f;
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
-        f32x4 p = Pf::mma(op.wf[hh][0], kf[0], op.bx[hh]);
-        p = Pf::mma(op.wf[hh][1], kf[1], p);
-        f32x4 hv = Pf::mma(op.sa[hh][0], vf[0], op.sz[hh]);
-        hv = Pf::mma(op.sa[hh][1], vf[1], hv);
+        G[hh] = Pf::mma(op.sa[hh][0], vf[0], op.sz[hh]);
+        G[hh] = Pf::mma(op.sa[hh][1], vf[1], G[hh]);
+      }
+      if (more) load_rows16(vf, V + (size_t)bh * L * kD, t + 16, L);
+      float D = 1.f;
+      if constexpr (KN == kCos) D = cM * expf(s2half * dot_rows(kf, kf));
+      f32x4 p[2];
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        p[hh] = Pf::mma(op.wf[hh][0], kf[0], op.bx[hh]);
+        p[hh] = Pf::mma(op.wf[hh][1], kf[1], p[hh]);
+      }
+      if (more) load_rows16(kf, K + (size_t)bh * L * kD, t + 16, L);
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          kh[hh][j] = feature<KN, Pf>(p[j], op.bx[hh][j]);
-          dot = fmaf(hv[j], kh[hh][j], dot);
-          G[hh][j] = sgn * hv[j] * feature_slope<KN, Pf>(p[j], op.bx[hh][j]);
+          kh[hh][j] = feature<KN, Pf>(p[hh][j], op.bx[hh][j]);
+          dot = fmaf(G[hh][j], kh[hh][j], dot);
+          G[hh][j] = sgn * G[hh][j] * feature_slope<KN, Pf>(p[hh][j], op.bx[hh][j]);
         }
-      }
       // the columns of k this wave's sums are finished with
       constexpr int NU = 8 / NW;
       constexpr int NQ = NW >= 4 ? 1 : 4 / NW;
@@ -301,7 +320,6 @@ __global__ __launch_bounds__(64 * f32_waves(M), 2) void k_bwd_dkv_f32(
         for (int q = 0; q < NQ; ++q)
           k4[q] = load_quad(K + (size_t)bh * L * kD, t, L, (w + q * NW) & 3);
       }
-      if (item + 1 < last) load_block(item + 1);
       const f32x8 gb = Pf::pack(G[0], G[1]);
       const f32x8 kb8 = Pf::pack(kh[0], kh[1]);
 #pragma unroll
