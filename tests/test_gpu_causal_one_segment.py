@@ -14,17 +14,20 @@ S64 = 64 ** -0.25
 
 
 # one chunk and less, whole and ragged chunks; one segment by length, by
-# descriptor (segment >= L) or by head count (more heads than CUs)
-@pytest.mark.parametrize("B,H,L,segment", [(1, 2, 1, 0), (2, 2, 63, 0), (1, 3, 128, 0),
-                                           (1, 2, 191, 0), (1, 2, 700, 704), (33, 8, 300, 0)])
-@pytest.mark.parametrize("M,chunk", [(64, 0), (112, 64), (128, 0), (208, 64), (256, 0), (256, 32)])
-@pytest.mark.parametrize("kernel", ["softmax", "relu"])
-@pytest.mark.parametrize("state", [False, True])
+# descriptor (segment >= L) or by head count (more heads than CUs; two of the
+# combinations)
+SIZES = ((1, 2, 1, 0), (2, 2, 63, 0), (1, 3, 128, 0), (1, 2, 191, 0), (1, 2, 700, 704),
+         (33, 8, 300, 0))
+FEATURES = ((64, 0), (112, 64), (128, 0), (208, 64), (256, 0), (256, 32))
+
+
+@pytest.mark.parametrize("state,kernel,M,chunk,B,H,L,segment", [
+    (state, kernel, *mc, *size) for state in (False, True) for kernel in ("softmax", "relu")
+    for mc in FEATURES for size in SIZES
+    if size[0] < 30 or (mc[0], state) in ((256, True), (112, False))])
 def test_one_segment(B, H, L, segment, M, chunk, kernel, state):
     import torch
     fv = __import__("paper_2006_03555_amd")
-    if B > 30 and (M, state) not in ((256, True), (112, False)):
-        pytest.skip("many heads are run on two of the combinations")
     kn = favor.KERNEL_RELU if kernel == "relu" else favor.KERNEL_SOFTMAX
     Q, K, V = wl.make_qkv(wl.Workload("t", "causal", B, H, L, 64, M, "bf16", M + L))
     W, b = favor.orf_draw(23, H, M, 64)

@@ -35,6 +35,9 @@ def test_default_scan_no_less_precise(L, M, kernel):
         # rows whose denominator cancels would carry the whole norm: medians over rows
         d = np.linalg.norm(to_host(out) - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
         err[chunk] = np.median(d)
-    # features and weights share their roundings; the intra-chunk weights' own part
-    # is a few percent of the error, so a tenth covers the sampling of the rows
-    assert err[0] <= 1.1 * err[64], err
+    # the two share the roundings of the features, and both are compared over the same
+    # rows; what differs is the intra-chunk weights' rounding. As two bf16 terms: at most
+    # 0.98 of the other scan's error (L 700, softmax), as one term at least 1.03
+    ratio = err[0] / err[64]
+    print(f"\n{kernel} M {M} L {L}: {ratio:.4f}", flush=True)
+    assert ratio <= 1.005, err
