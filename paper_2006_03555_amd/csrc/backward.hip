@@ -271,15 +271,12 @@ __device__ __forceinline__ void query_grad(
   using P = Mma<T>;
   using frag = typename P::frag;
   constexpr float sgn = KN == kCos ? -1.f : 1.f;
-  // two feature steps per unrolled iteration; at M = 64 (two steps in all) a
-  // full unroll would spill, so the loop stays rolled
-  constexpr int kFeatureUnroll = M > 64 ? 2 : 1;
   const int l = lane_id();
   const int g = l >> 4;
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb) dacc[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
   dot2 = 0.f;
-#pragma unroll kFeatureUnroll
+#pragma unroll 1   // two steps in all: a full unroll would spill
   for (int sidx = s0; sidx < s1; ++sidx) {
     f32x4 G[2];
 #pragma unroll
@@ -309,13 +306,13 @@ __device__ __forceinline__ void query_grad(
 }
 
 // dQ row store: dQ = WT G + alpha s^2 (g~ . q-hat) q (cos features).
-// Store 8 consecutive values, or (ACC) add them to what dst holds: the fp32
-// gradients of a feature slice after the first (a gradient is a sum over
-// features, see the launchers), or the gradient of one direction onto the
-// other's when both are differentiated in one call (bf16 too: one more
-// rounding of the sum).
+// Store 8 consecutive values, or (ACC, fp32) add them to what dst holds: the
+// gradients of a feature slice after the first (a gradient is a sum over features,
+// see the launchers), or the gradient of one direction onto the other's when both
+// are differentiated in one call.
 template <bool ACC, typename T>
 __device__ __forceinline__ void put8(T *p, f32x4 a, f32x4 b) {
+  static_assert(!ACC || sizeof(T) == 4, "bf16 gradients are not added up here");
   if constexpr (ACC) {
     float v[8];
     load8_f32(p, v);
@@ -518,16 +515,17 @@ __global__ __launch_bounds__(kBwdBidirThreads) void k_bwd_dq(
 }
 
 // ------------------------------------------------------------ causal dQ
-// The segment-scan kernels run eight waves: wave w works on row block w % 4 of
-// the chunk over half hf = w / 4 of the feature steps (the two halves' partial
-// sums meet in LDS), and on FB feature blocks of the carried state.
+// The segment-scan kernels (fp32; bf16: feature_scan.hip) take M = 64 features a
+// launch and run eight waves: wave w works on row block w % 4 of the chunk over half
+// hf = w / 4 of the feature steps (the two halves' partial sums meet in LDS); the first
+// four also hold a 16-feature block of the carried state each.
 constexpr int kScanThreads = 512;
 template <int M>
 struct ScanSplit {
-  static constexpr int NB = M / 16;                 // feature blocks
-  static constexpr int FB = NB >= 8 ? NB / 8 : 1;   // blocks per state wave
-  static constexpr int FW = NB / FB;                // waves holding state (4 or 8)
-  static constexpr int NS = M / 32;                 // feature steps
+  static constexpr int FB = 1;         // feature blocks per state wave
+  static constexpr int FW = M / 16;    // waves holding state
+  static constexpr int NS = M / 32;    // feature steps
+  static_assert(FW == 4, "eight waves, four of them with state");
 };
 
 template <typename T, int M>
@@ -737,9 +735,6 @@ __device__ __forceinline__ void key_grad(
   using P = Mma<T>;
   using frag = typename P::frag;
   constexpr float sgn = KN == kCos ? -1.f : 1.f;
-  // two feature steps per unrolled iteration; at M = 64 (two steps in all) a
-  // full unroll would spill, so the loop stays rolled
-  constexpr int kFeatureUnroll = M > 64 ? 2 : 1;
   const int l = lane_id();
   const int g = l >> 4;
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
@@ -751,7 +746,7 @@ __device__ __forceinline__ void key_grad(
     p4[k] = zero4;
   }
   doth = 0.f;
-#pragma unroll kFeatureUnroll
+#pragma unroll 1   // two steps in all: a full unroll would spill
   for (int sidx = s0; sidx < s1; ++sidx) {
     f32x4 kh[2], G[2];
 #pragma unroll
