@@ -36,8 +36,8 @@ other workload of the configuration list at its full size, each with its step
 time, per-kernel durations and the roofline of its dominant kernel
 (bidir_b8h8 and causal_b8h8 with the draw timed on its own beside the step,
 causal_b8h8 also over three causal segment lengths; causal_long with the
-redraw inside the timed step); the causal workloads also over both chunk
-lengths of the scan (64 and 32 tokens).
+redraw inside the timed step); the causal workloads also with each chunk length
+of the scan named (64 and 32 tokens), which run another kernel than the default.
 
 python bench.py --summarize-counters DIR turns rocprofv3 FETCH_SIZE /
 WRITE_SIZE runs (see summarize_counters) into profiles/traffic.json.
@@ -249,11 +249,6 @@ def measured_peaks(torch, fv):
     return out
 
 
-def default_chunk(w):
-    """The chunk length the library picks for chunk = 0 (favor_desc.chunk)."""
-    return 32 if w.dtype == "bf16" and w.M <= 128 else 64
-
-
 def bench_workload(name, args, torch, fv, segment_rows=(0,), chunks=(0,)):
     """One workload of the configuration list at its full size: the step is its
     attention call(s) over inputs resident in HBM, with the random-feature draw
@@ -325,7 +320,7 @@ def bench_workload(name, args, torch, fv, segment_rows=(0,), chunks=(0,)):
             for r in segment_rows}
     if len(chunks) > 1:
         entry["causal_chunk_tokens_sweep"] = {
-            str(c or default_chunk(w)): brief(sweep[(segment_rows[0], c)]) for c in chunks}
+            str(c or "library default"): brief(sweep[(segment_rows[0], c)]) for c in chunks}
     if not w.redraw:
         draw = lambda i: fv.orf_draw(1000 + i, H, M, w.d, W=Wd, b=bd, stream=st)
         for i in range(args.warmup):
@@ -463,12 +458,11 @@ def main():
     ap.add_argument("--workload", default="protein_b4h8", choices=sorted(wl.WORKLOADS))
     ap.add_argument("--segment", type=int, default=0,
                     help="rows per segment of the causal scan (a multiple of 64; 0 = the "
-                         "library's choice, one workgroup per CU with 64-token chunks, two "
-                         "with 32) for the forward steps")
+                         "library's choice, one workgroup per CU, two with 32-token chunks "
+                         "or bf16 inputs and M <= 128) for the forward steps")
     ap.add_argument("--chunk", type=int, default=0, choices=(0, 32, 64),
                     help="tokens per step of the causal scan for the forward steps (0 = the "
-                         "library's choice: 32 for bf16 inputs with M <= 128, else 64); the "
-                         "causal workloads also time the other")
+                         "library's choice); the causal workloads also time the others")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-variants", action="store_true",
                     help="skip the ReLU, unnormalised and backward variants (profiler runs "
@@ -866,8 +860,8 @@ def main():
         for name in names:
             causal = wl.WORKLOADS[name].direction != "bidir"
             rows = (0, 1024, 4096) if name == "causal_b8h8" else (0,)
-            first = args.chunk or default_chunk(wl.WORKLOADS[name])
-            chunks = (args.chunk, 64 if first == 32 else 32) if causal else (0,)
+            # the library's choice (0) is a scan of another form than a named length
+            chunks = (args.chunk, *(c for c in (0, 64, 32) if c != args.chunk)) if causal else (0,)
             others[name] = bench_workload(name, args, torch, fv, segment_rows=rows,
                                           chunks=chunks)
 
@@ -887,7 +881,7 @@ def main():
         "config": {"workload": w.name, "B": w.B, "H": w.H, "L": w.L, "d": w.d, "M": M,
                    "direction": w.direction, "orf_draw_per_step": True,
                    "causal_segment_rows": args.segment or "library default",
-                   "causal_chunk_tokens": args.chunk or default_chunk(w),
+                   "causal_chunk_tokens": args.chunk or "library default",
                    "orf_draw": "drawn in line before the attention pass, same stream",
                    "parallelism": "single GPU"},
         "kernels": kernels,

@@ -28,8 +28,9 @@
  * inputs and M > 128 runs as two passes over the feature halves);
  * 0 <= L <= 2^30 (any length, ragged tails handled; L = 0 is a no-op); B, H >= 0,
  * B*H <= 65535; in_dtype F32 or BF16; out_dtype F32 or BF16. F32 inputs use
- * fp32 matrix cores and an accurately rounded cosine; BF16 inputs use bf16
- * matrix cores with fp32 accumulation, the hardware cosine and bf16 features.
+ * fp32 matrix cores and a cosine of at most 1.4e-7 absolute error (rms 2.0e-8);
+ * BF16 inputs use bf16 matrix cores with fp32 accumulation, the hardware cosine
+ * and bf16 features.
  */
 #ifndef FAVOR_H
 #define FAVOR_H
@@ -89,9 +90,9 @@ typedef struct {
   int32_t chunk;            /* causal chunk length T: tokens per step of the
                                prefix-sum scan (Sec. 2.5.1): 64 (four 16-token
                                matrix-core blocks in the intra-chunk product) or,
-                               for bf16 inputs, 32; 0 = the library's choice (bf16
-                               inputs: 64-token steps of the form that measured
-                               fastest; fp32: 64). Other values,
+                               for bf16 inputs, 32; 0 = the library's choice (of
+                               the scan's form as well as its step; fp32: 64).
+                               Other values,
                                and 32 with fp32 inputs in a causal call, return
                                FAVOR_ERR_UNSUPPORTED. The result is the same sum
                                in another grouping                                 */

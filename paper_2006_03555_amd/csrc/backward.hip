@@ -16,13 +16,16 @@
 //   R = sum of q-hat_i (x) u~_i over the rows that see key j (all rows, or i >= j),
 //   dK'_j = R C_j,  dV_j = D~_K R^T k-hat_j (first d columns),
 //   dK = D~_K [s^2 (h . k-hat) k - (h o sin) (s W)] with h = dK', or (h o step) W''.
-// Kernels:
-//   k_bwd_dq     per row tile (bidirectional, persistent) or per 64-token chunk
+// Kernels (the causal ones of bf16 inputs are feature_scan.hip's, the bidirectional
+// ones of fp32 inputs backward_f32.hip's but for dQ of many rows, see f32_dq_tiles):
+//   k_bwd_dq, k_bwd_dq_scan
+//                per row tile (bidirectional, persistent) or per 64-token chunk
 //                (causal): projection, features and slopes of its queries on the
 //                matrix cores, g~ = S u plus, causal, the keys of the chunk up to
 //                the query (tril(C~ u^T) against the chunk's key features), the
 //                input-gradient product with W''^T; writes dQ and (alpha, alpha u_d)
-//   k_bwd_dkv    per key tile / chunk: key features and slopes, h = R C_j plus,
+//   k_bwd_dkv, k_bwd_dkv_scan
+//                per key tile / chunk: key features and slopes, h = R C_j plus,
 //                causal, the queries of the chunk from the key on; dV = R^T k-hat plus,
 //                causal, tril-transposed (q-hat . k-hat) u~; dK as above
 //   k_sum_splits fixed-order sum of split partials (Buf1, dBuf1)

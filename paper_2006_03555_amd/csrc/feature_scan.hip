@@ -596,11 +596,11 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
   const float2 *auh = FWD ? nullptr : aux + (size_t)bh * L;
   const int jb = w & 3;
 
-  // the next chunk's rows: queries and keys to be staged, and the output
-  // gradients this wave transposes (row block w % 4, columns 32 (w / 4 + k) ..)
+  // the next chunk's rows: x and z to be staged, and the u rows this wave
+  // transposes (row block w % 4, columns 32 (w / 4 + k) ..)
   struct Regs {
     frag z[RPT], x[RPT], u[RPT];
-    float2 a[FWD ? 1 : 4];   // dV: row weights of queries 16 (w % 4) + 4 g + j
+    float2 a[FWD ? 1 : 4];   // dV: row weights of z rows 16 (w % 4) + 4 g + j
   };
   Regs rg;
   auto load_rows = [&](int t0) __attribute__((always_inline)) {
@@ -657,7 +657,7 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
     bx[mb] = *reinterpret_cast<const f32x4 *>(bp + 4 * g);
     bz[mb] = bp[c16];
   }
-  // R: rows = features 16 (w FB + mb) + 4 g + j, lane = value column perm_col(nb, c16)
+  // The aggregate: rows = features 16 (w FB + mb) + 4 g + j, lane = value column perm_col(nb, c16)
   // (block 4: the last column, replicated)
   f32x4 acc[FB][5];
   {
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
 
   for (int c = 0; c < nch; ++c) {
     const int t0 = chunk_t0(c);
-    // (alpha dout)^T and its last column
+    // (w u)^T and u~'s last column
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
       const int tb = w & 3;
@@ -728,7 +728,7 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
       if (kh == 0 && c16 == 0)
         store_half_frag(&sm.UE[tb >> 1][g], tb & 1, ez);
     }
-    // R^T before the chunk's rows
+    // the aggregate without the chunk's rows
 #pragma unroll
     for (int nb = 0; nb < 5; ++nb) {
       if constexpr (FB == 2) {
@@ -744,7 +744,7 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
           store_half_frag(&sm.RE[w >> 1][g], w & 1, acc[0][nb]);
       }
     }
-    // key features, lane = key
+    // features of the x rows, lane = x
 #pragma unroll
     for (int tb = 0; tb < 4; ++tb) {
       const frag x0 = load_frag<bf16>(&sm.X[tile_at<kWide>(16 * tb + c16, g)]);
@@ -762,8 +762,8 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
       else
         store_half_frag(&sm.KF[tb][w >> 1][l], w & 1, f[0]);
     }
-    // query features as A operand of the fold (row = feature, k = queries), and
-    // transposed on the matrix cores (exact) with lane = query
+    // features of the z rows as A operand of the fold (row = feature, k = z rows), and
+    // transposed on the matrix cores (exact) with lane = z
     frag zt[FB][2];
 #pragma unroll
     for (int zs = 0; zs < 2; ++zs) {
@@ -797,7 +797,7 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
     __syncthreads();
 
     if (c + 1 < nch) load_rows(chunk_t0(c + 1));
-    // fold the chunk's rows into R
+    // fold the chunk's z rows into the aggregate
 #pragma unroll
     for (int zs = 0; zs < 2; ++zs)
 #pragma unroll
@@ -806,7 +806,7 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
 #pragma unroll
         for (int mb = 0; mb < FB; ++mb) acc[mb][nb] = P::mma(zt[mb][zs], u, acc[mb][nb]);
       }
-    // key block jb against the query half (wide) or both halves
+    // x block jb against one half of the z rows (wide) or both
     frag kf[NS];
 #pragma unroll
     for (int ks = 0; ks < NS; ++ks) kf[ks] = sm.KF[jb][ks][l];
@@ -864,7 +864,7 @@ __global__ __launch_bounds__(64 * scan_waves(M), scan_wide(M) ? 1 : 2) void k_ou
         va[nb] = P::mma(u, pl, va[nb]);
       }
     }
-    // R^T k-hat (wide: this half's feature steps)
+    // a^T xf (wide: this half's feature steps)
     constexpr int kSteps = kWide ? NS / 2 : NS;
     const int kb = kWide ? (w >> 2) * kSteps : 0;
 #pragma unroll

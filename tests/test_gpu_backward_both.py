@@ -82,8 +82,8 @@ def test_both_backward_parity(B, H, L, M, dtype, kernel, renorm, eps, states):
                                            ("bf16", 64, 0), ("f32", 64, 0)])
 def test_both_backward_reads_saved_forward_quantities(dtype, M, chunk):
     """Given the workspace of the attn_both call (W'', b'', Buf1 and the segment
-    prefixes; 32-token chunks at M <= 128 in bf16, and when asked for at
-    M = 256, the segment plan of two workgroups per CU), the gradients are
+    prefixes; bf16 at M <= 128, and at M = 256 with 32-token chunks, the segment plan
+    of two workgroups per CU), the gradients are
     bitwise those of recomputing them; given also
     its outputs and row scales, within the gate of recomputing them. The causal
     state gradient is bitwise that of attn_causal_backward."""
