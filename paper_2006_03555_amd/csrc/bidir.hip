@@ -468,7 +468,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 2 : 1) void k_qside(const T *
 // Measured against k_qside on the same calls (us): fp32 M 256, 1024 row blocks
 // 18.4 against 26.3, 2048 blocks 33.6 against 29.0; fp32 M 128, 1024 blocks 11.0
 // against 15.6; bf16 M 256, 256 / 512 / 1024 blocks 3.9 / 5.3 / 8.0 against
-// 8.9 / 8.8 / 9.2 (and slower at 2048: each row block reads W'' and Buf1 again).
+// 8.9 / 8.8 / 9.2 (and slower at 2048: each row block reads W'' and Buf1 again). Whole
+// bf16 calls at 1024 blocks, before k_qside_split and the shorter key splits / with
+// them: B1 H8 L2048 M128 19.2 / 16.5, M64 16.3 / 14.2, B1 H4 L4096 M128 19.7 / 16.9.
 constexpr int kQsideSplitMaxBlocks = 1024;
 
 template <typename T, typename To, int M, int KN, int FIN, bool SAVE>

@@ -31,10 +31,11 @@ struct Shape {
   int chunk;     // tokens per step of the causal scan: 64, or 32 (bf16 inputs)
   // causal scan of bf16 inputs: k_out_scan (64-token chunks, products over all
   // features through LDS) where the caller leaves the chunk length to the library and
-  // a head has several segments, else k_causal_fs with `chunk`. Per launch (us): B4 H8 L8192 M256
-  // 71.7 against 82.1 (T = 64), B1 H16 L65536 M256 289 against 311, B8 H8 L2047
-  // M128 25.4 against 27.6 (T = 32). Whole calls: both directions of B4 H8 L8192
-  // 161 -> 151, B1 H16 L65536 389 -> 354.
+  // a head has several segments, else k_causal_fs with `chunk`. Per launch, traced
+  // (us), k_causal_fs / k_out_scan: B4 H8 L8192 M256 72.3 / 62.8, B8 H8 L8192 137.7 /
+  // 121.6, B1 H16 L65536 278 / 249. M = 64 as whole calls, k_causal_fs with
+  // T = 32: B8 H8 L2047 39.4 / 36.7, B4 H8 L8192 62.3 / 56.3, B1 H16 L32768 109.7 / 96.2,
+  // both directions 49.4 / 46.3, 77.9 / 71.9, 137.3 / 124.1.
   int feature_scan;
 };
 
