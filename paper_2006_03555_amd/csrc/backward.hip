@@ -17,7 +17,7 @@
 //   dK'_j = R C_j,  dV_j = D~_K R^T k-hat_j (first d columns),
 //   dK = D~_K [s^2 (h . k-hat) k - (h o sin) (s W)] with h = dK', or (h o step) W''.
 // Kernels (the causal ones of bf16 inputs are feature_scan.hip's, the bidirectional
-// ones of fp32 inputs backward_f32.hip's but for dQ of many rows, see f32_dq_tiles):
+// ones of fp32 inputs backward_f32.hip's but for many rows at small M, see f32_tiles):
 //   k_bwd_dq, k_bwd_dq_scan
 //                per row tile (bidirectional, persistent) or per 64-token chunk
 //                (causal): projection, features and slopes of its queries on the
@@ -394,7 +394,7 @@ struct DqSmem {
 
 // Items are (head, tile of 8 waves x TBW x 16 rows), walked persistently over
 // XCD-local ranges; Buf1 [BH][M][65] fp32. A wave takes its TBW row blocks through
-// one pass over the features. fp32 takes one block (see f32_dq_tiles), bf16 two, so
+// one pass over the features. fp32 takes one block (see f32_tiles), bf16 two, so
 // every operand read from LDS (12 KB per 32 features) meets both: with one block at a
 // time those reads alone were half of the bf16 kernel. Two blocks fit 256 registers
 // (two waves per SIMD). B4 H8 L8192 M256: dQ
@@ -832,7 +832,7 @@ __device__ __forceinline__ void store_vgrad(T *dst, const f32x4 (&vacc)[4], floa
     put8<ACC>(dst + 32 * pp + 8 * g, vacc[2 * pp] * D, vacc[2 * pp + 1] * D);
 }
 
-// ------------------------------------------------------------ bidirectional dK, dV (bf16)
+// ------------------------------------------------------------ bidirectional dK, dV
 template <typename T, int M>
 struct DkvSmem {
   using frag = typename Mma<T>::frag;
@@ -1326,14 +1326,15 @@ static hipError_t bidir_dq_bf16(const Shape &sh, const BwdArgs &a, hipStream_t s
   FAVOR_BWD_DISPATCH_M(sh.M, return bidir_dq<bf16, MM, kBwdTbw>(sh, a, st));
 }
 
-// fp32 dQ with M <= 128 by tiles of 128 rows and one workgroup per CU (k_bwd_dq, its
-// operands in LDS) where the tiles are at least nine tenths full and give every CU
-// the same number: it then takes less time per row than k_bwd_dq_f32, whose waves hold
-// the operands and each load every row. Forward and backward (us), k_bwd_dq_f32 / this
-// one: cos features M128 B4 H8 L2048 193.9 / 186.2, B8 H8 L4096 636.6 / 616.1, B6 H8
-// L4000 533.4 / 522.0, and three quarters full, B3 H8 L2048, 173.6 / 177.9; ReLU M64 B2
-// H8 L2048 86.4 / 83.0, B8 H8 L4096 374.6 / 365.2.
-static bool f32_dq_tiles(const Shape &sh) {
+// fp32 inputs by tiles of 128 rows and one workgroup per CU (k_bwd_dq with M <= 128,
+// k_bwd_dkv with M = 64) where the tiles are at least nine tenths full and give every CU
+// the same number: that then takes less time per row than the kernels of
+// backward_f32.hip, whose waves hold the operands and each load every row. Forward and
+// backward (us), backward_f32.hip / this: cos features M128 B4 H8 L2048 193.9 / 186.2,
+// B8 H8 L4096 636.6 / 616.1, B6 H8 L4000 533.4 / 522.0, and three quarters full, B3 H8
+// L2048, 173.6 / 177.9; ReLU M64 B2 H8 L2048 86.4 / 80.1, B8 H8 L4096 374.6 / 358.4 (83.0
+// and 364.6 with dQ alone).
+static bool f32_tiles(const Shape &sh) {
   const long long rows = kBwdBidirThreads / 4;
   const long long tiles = sh.BH * ((sh.L + rows - 1) / rows);
   const long long rounds = (tiles + kBwdMaxWorkgroups - 1) / kBwdMaxWorkgroups;
@@ -1346,7 +1347,7 @@ hipError_t launch_bwd_dq(const Shape &sh, Dt in, bool causal, const BwdArgs &a, 
     return in == Dt::BF16 ? launch_bwd_dq_scan(sh, a, accumulate, st)
                           : causal_dq_f32(sh, a, st, accumulate);
   if (in == Dt::BF16) return bidir_dq_bf16(sh, a, st);
-  if (f32_dq_tiles(sh))
+  if (f32_tiles(sh))
     return sh.M == 64 ? bidir_dq<float, 64, 1>(sh, a, st) : bidir_dq<float, 128, 1>(sh, a, st);
   return launch_bwd_dq_f32(sh, a, st);
 }
@@ -1373,27 +1374,32 @@ static hipError_t causal_dkv_f32(const Shape &sh, const BwdArgs &a, hipStream_t 
   });
 }
 
-static hipError_t bidir_dkv_bf16(const Shape &sh, const BwdArgs &a, hipStream_t st) {
-  using T = bf16;
-  const int rows = kBwdBidirThreads / 4 * kBwdTbw;
+template <typename T, int M, int TBW>
+static hipError_t bidir_dkv(const Shape &sh, const BwdArgs &a, hipStream_t st) {
+  const int rows = kBwdBidirThreads / 4 * TBW;
   const int ntiles = (sh.L + rows - 1) / rows;
   const int nitems = ntiles * sh.BH;
   dim3 grid(min(nitems, kBwdMaxWorkgroups));
   return bwd_variant(sh, [&](auto kn, auto) -> hipError_t {
     constexpr int KN = decltype(kn)::value;
-    FAVOR_BWD_DISPATCH_M(sh.M,
-        hipLaunchKernelGGL((k_bwd_dkv<T, MM, KN, kBwdTbw>), grid, dim3(kBwdBidirThreads), 0, st,
-                           (const T *)a.K, (const T *)a.V, (const Mma<T>::frag *)a.wfr, a.bq,
-                           a.W, a.state, (T *)a.dK, (T *)a.dV, sh.H, sh.L, sh.s, sh.Mr,
-                           feature_norm(sh), wt_scale(sh), ntiles, nitems));
+    hipLaunchKernelGGL((k_bwd_dkv<T, M, KN, TBW>), grid, dim3(kBwdBidirThreads), 0, st,
+                       (const T *)a.K, (const T *)a.V, (const typename Mma<T>::frag *)a.wfr,
+                       a.bq, a.W, a.state, (T *)a.dK, (T *)a.dV, sh.H, sh.L, sh.s, sh.Mr,
+                       feature_norm(sh), wt_scale(sh), ntiles, nitems);
     return hipGetLastError();
   });
+}
+
+static hipError_t bidir_dkv_bf16(const Shape &sh, const BwdArgs &a, hipStream_t st) {
+  FAVOR_BWD_DISPATCH_M(sh.M, return bidir_dkv<bf16, MM, kBwdTbw>(sh, a, st));
 }
 
 hipError_t launch_bwd_dkv(const Shape &sh, Dt in, bool causal, const BwdArgs &a, hipStream_t st) {
   if (causal)
     return in == Dt::BF16 ? launch_bwd_dkv_scan(sh, a, st) : causal_dkv_f32(sh, a, st);
-  return in == Dt::BF16 ? bidir_dkv_bf16(sh, a, st) : launch_bwd_dkv_f32(sh, a, st);
+  if (in == Dt::BF16) return bidir_dkv_bf16(sh, a, st);
+  return sh.M == 64 && f32_tiles(sh) ? bidir_dkv<float, 64, 1>(sh, a, st)
+                                     : launch_bwd_dkv_f32(sh, a, st);
 }
 
 }  // namespace favor

@@ -10,8 +10,8 @@
 // them; what a launch of few rows (B2 H8 L1024: 1024 row blocks) needs is all CUs
 // at work and no chain of feature steps. Walking a 256-row tile per workgroup with
 // the operand tables in LDS, 128 features at a time, took 2 x 39 us (dQ) and 2 x
-// 48 us (dK, dV) there on 64 workgroups. (dQ of M <= 128 with enough rows to give every
-// CU full tiles takes that form all the same: f32_dq_tiles in backward.hip.)
+// 48 us (dK, dV) there on 64 workgroups. (Calls of M <= 128 with enough rows to give
+// every CU full tiles take that form all the same: f32_tiles in backward.hip.)
 // A block's rows are loaded while the block before is worked on, each tensor's once
 // that block's fragments of it are dead: loaded together after them, one third of the
 // block before their use, many rows took longer (forward and backward of B8 H8 L4096

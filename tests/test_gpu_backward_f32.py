@@ -42,7 +42,8 @@ def test_rows(kind, M, B, H, L):
     _check_all(_host_grads(got), ref, "f32", scale)
 
 
-# dQ by 128-row tiles: 256 tiles, the last of each head one row short or a tenth empty
+# Gradients by 128-row tiles (dQ; at M = 64 dK and dV too): 256 tiles, the last of each
+# head one row short or the tiles a tenth empty
 @pytest.mark.parametrize("kind", list(KINDS))
 @pytest.mark.parametrize("M,L", [(64, 2047), (80, 2047), (128, 2047), (128, 1850)])
 def test_full_tiles(kind, M, L):
@@ -56,8 +57,8 @@ def test_full_tiles(kind, M, L):
     q, k, v, do = ((torch.randn((B, H, L, 64), generator=gen) * s).cuda()
                    for s in (S64, S64, 1.0, 1.0))
     W, b = fv.orf_draw(7, H, M)
-    dQ = torch.full_like(q, float("nan"))
-    got = fv.attn_bidir_backward(q, k, v, W, b, S64, do, dQ=dQ, **kw)[0]
+    g3 = [torch.full_like(q, float("nan")) for _ in range(3)]
+    got = fv.attn_bidir_backward(q, k, v, W, b, S64, do, dQ=g3[0], dK=g3[1], dV=g3[2], **kw)
 
     def phi(x):
         p = x * S64 @ W.double().transpose(-1, -2).contiguous()
@@ -66,17 +67,17 @@ def test_full_tiles(kind, M, L):
         d = torch.exp(0.5 * (x * S64).square().sum(-1, keepdim=True))
         return d * (2.0 / M) ** 0.5 * torch.cos(p + b.double()[:, None, :])
 
-    x = q.double().requires_grad_()
-    ones = torch.cat([v.double(), torch.ones_like(v[..., :1]).double()], -1)
-    buf = phi(x) @ (phi(k.double()).transpose(-1, -2).contiguous() @ ones)
+    xs = [x.double().requires_grad_() for x in (q, k, v)]
+    ones = torch.cat([xs[2], torch.ones_like(xs[2][..., :1])], -1)
+    buf = phi(xs[0]) @ (phi(xs[1]).transpose(-1, -2).contiguous() @ ones)
     out = buf[..., :64]
     if kw.get("renormalize", True):
         out = out / (buf[..., 64:] + kw.get("denom_eps", 0.0))
-    ref, = torch.autograd.grad(out, x, do.double())
-    # 1.2e-6 where a denominator divides, 4e-7 else, as the other sizes measure
-    assert float((got - ref).norm() / ref.norm()) <= 5e-6
-    # and no row is far off: a row's error against the larger of its own size and the
-    # mean row's. Denominators that cancel amplify their rounding, so the worst rows of
-    # cos features are looked at only for a wrong row (order 1)
-    size = ref.norm(dim=-1).clamp(min=float(ref.norm(dim=-1).mean()))
-    assert float(((got - ref).norm(dim=-1) / size).max()) <= (1e-4 if relu else 1e-2)
+    for x, ref in zip(got, torch.autograd.grad(out, xs, do.double())):
+        # at most 1.2e-6 at the other sizes
+        assert float((x - ref).norm() / ref.norm()) <= 5e-6
+        # and no row is far off: a row's error against the larger of its own size and the
+        # mean row's. Denominators that cancel amplify their rounding, so the worst rows
+        # of cos features are looked at only for a wrong row (order 1)
+        size = ref.norm(dim=-1).clamp(min=float(ref.norm(dim=-1).mean()))
+        assert float(((x - ref).norm(dim=-1) / size).max()) <= (1e-4 if relu else 1e-2)
